@@ -146,6 +146,34 @@ def test_linear_headline_shapes_sampled_rows(N, resid):
                      f64(a[rows]), f64(w), None if r is None else f64(r[rows]))
 
 
+# One shape per output tile (256 x 256, 256 x 128, 128 x 128, 64 x 128, 64 x 64,
+# each the cheapest in rounds over the CUs), rows and k slices off the tile and
+# ring edges: every row on a tile or block edge and the ragged last ones
+# against the oracle, and alone (its own call, in a 64 x 64 tile) bit for bit.
+@pytest.mark.parametrize("M,N,K,resid", [
+    (1537, 9216, 192, True),
+    (600, 9344, 64, False),
+    (300, 9216, 320, True),
+    (150, 9216, 448, False),
+    (65, 384, 192, True),
+])
+def test_linear_every_tile(M, N, K, resid):
+    a, w = _bf((M, K), 41 + M), _bf((N, K), 42 + N, K ** -0.5)
+    r = _bf((M, N), 43 + K) if resid else None
+    a_d, w_d, r_d = a.to(DEV), w.to(DEV), None if r is None else r.to(DEV)
+    got = rc.linear(a_d, w_d, residual=r_d)
+    rows = sorted({i + d for i in range(0, M, 32) for d in (-1, 0) if 0 <= i + d} | {M - 1})[:40] + [M - 2, M - 1]
+    rows = sorted(set(rows))
+    torch.cuda.synchronize()
+    want = oc.project(f64(a[rows]), f64(w), None if r is None else f64(r[rows]))
+    check_projection(got[rows], want, f"linear tile M={M} N={N} K={K}", f64(a[rows]), f64(w),
+                     None if r is None else f64(r[rows]))
+    for i in (0, M // 2, M - 1):
+        alone = rc.linear(a_d[i:i + 1], w_d, residual=None if r is None else r_d[i:i + 1])
+        torch.cuda.synchronize()
+        assert torch.equal(alone, got[i:i + 1]), i
+
+
 # ------------------------------------------------------------- chained layers
 def _wl(name, B, H, D, lens_st_lt_x, refs, seed=42):
     st, lt, x = lens_st_lt_x
