@@ -183,7 +183,8 @@ int32_t rc_step_auto_splits(const rc_layout* L, int32_t B, int32_t H, int32_t D)
  * with the bf16 cache (fp8 = 0) or the FP8 cache (fp8 = 1), for occupancy
  * reports: *work_groups over all its launches (one per query tile and split;
  * the whole tiles plus two per split tile for RC_SPLITS_LAST_ROUND; 256 for
- * RC_SPLITS_BALANCED), *rows_per_wg the query rows per work-group,
+ * RC_SPLITS_BALANCED; a query tile or piece that runs as two work-groups of
+ * half its rows counts once), *rows_per_wg the query rows per work-group,
  * *splits_used the split count it resolves to (2 for the tail split,
  * RC_SPLITS_LAST_ROUND when that split applies and 1 when it does not,
  * RC_SPLITS_BALANCED for the balanced schedule).
@@ -194,7 +195,8 @@ rc_status rc_step_launch_shape(const rc_layout* L, int32_t B, int32_t H, int32_t
                                int64_t* work_groups, int32_t* rows_per_wg, int32_t* splits_used);
 
 /* Launch plan of rc_ref_kv_prefill (bf16 cache), for reports and tests:
- * *attn_wgs attention work-groups over all launches (one per query tile),
+ * *attn_wgs attention work-groups over all launches (one per query tile, two
+ * of half the rows counting once),
  * *copy_wgs copy work-groups appended to the (last) attention launch, and
  * *copy_rows the flat cache rows (b, h, row) [0, *copy_rows) that they
  * copy; the store kernel copies the other B * H * N_cached - *copy_rows rows

@@ -34,6 +34,9 @@ def build(verbose: bool = False) -> str:
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Wall", "-Wno-unused-function",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # the attention kernels read their by-value arguments at more than
+           # 300 places, beyond which LLVM would first copy them to scratch
+           "-mllvm", "-instcombine-max-copied-from-constant-users=4096",
            "-I", INCLUDE, "-I", CSRC,
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", tmp]
     if verbose:

@@ -219,6 +219,7 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
       t.rows = int32_t(cpl.rows);
       RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + cpl.blocks, "prefill attention"));
     }
+    p.half_tiles = half_tiles(p);
     c.row0 = cpl.rows;
     const int64_t rest = int64_t(B) * H * n_cached - cpl.rows;
     RC_TRY(check_blocks((rest * (D / 8) + 255) / 256, "cache store"));
@@ -243,6 +244,7 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   for (int i = 0; i < n_copy; ++i) c.seg[i] = seg[i];
   // the quantising store's grids: (B H) x row blocks (amax), one thread per
   // 16-byte granule of K and of V
+  p.half_tiles = half_tiles(p);
   RC_TRY(check_blocks(int64_t(B) * H, "FP8 cache store"));
   RC_TRY(check_blocks((int64_t(B) * H * n_cached * (D / 8) + 255) / 256, "FP8 cache store"));
   RC_TRY(hip_status(launch_attention(p, D, stream), "prefill attention launch"));
@@ -273,6 +275,7 @@ rc_status plan_step(const rc_layout* L, int32_t D, bool fp8, int32_t splits, Par
     p.bal_wgs = kBalancedWGs;
     return RC_OK;
   }
+  p.half_tiles = half_tiles(p);
   return check_grid(p);
 }
 
@@ -584,6 +587,7 @@ rc_status rc_full_attention_ws(const rc_layout* L, int32_t B, int32_t H, int32_t
       p.lr_tiles = T;
       p.ws_o = static_cast<float*>(workspace);
       p.ws_ml = p.ws_o + size_t(2) * T * p.bm * D;
+      p.half_tiles = half_tiles(p);
       RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + T, "full attention"));
       RC_TRY(hip_status(launch_attention(p, D, stream), "full attention launch"));
       RC_TRY(hip_status(launch_combine_last_round(p, D, stream), "last-round merge launch"));
@@ -591,6 +595,7 @@ rc_status rc_full_attention_ws(const rc_layout* L, int32_t B, int32_t H, int32_t
     }
     p.tail_num = 0;
   }
+  p.half_tiles = half_tiles(p);
   RC_TRY(hip_status(launch_attention(p, D, stream), "full attention launch"));
   return RC_OK;
 }

@@ -316,10 +316,9 @@ __device__ __forceinline__ bf16x8 k_frag(const uint16_t* ks, const FragBase& fb,
 
 // S^T = K Q^T for sub-tile j (kKB 32x32 accumulators per query block);
 // src.k(f) reads K fragment f of the stage.
-template <int D, int QB, class Src>
+template <int D, int QB, int KB, class Src>
 __device__ __forceinline__ void s_part(const Src& src, int j, const bf16x8 (&qf)[QB][D / 16],
-                                       f32x16 (&sacc)[QB][Blk<QB>::kKB]) {
-  constexpr int KB = Blk<QB>::kKB;
+                                       f32x16 (&sacc)[QB][KB]) {
   constexpr int NDC = D / 16;
   constexpr int NF = KB * NDC;
   constexpr int PF = Blk<QB>::kPF;
@@ -443,6 +442,17 @@ __device__ __forceinline__ void softmax_part(int lane, int valid, f32x16 (&sacc)
 // the exact path up front: tile max, then the weights.
 constexpr float kSumLimit = 65536.f;
 
+// The lane index computed afresh (v_mbcnt over a full mask) where it is
+// needed: written as inline assembly so that the compiler neither hoists it
+// out of the tile loop nor keeps it live across the phases, where a register
+// is only to be had by spilling (a spilled lane index costs a scratch reload,
+// a full memory latency, in the phase that issues the tile loads).
+__device__ __forceinline__ int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
 // p = 2^a for one block into P^T (bf16); returns the per-lane fp32 sum of p
 // in four independent chains of plain adds.  (v_dot2_f32_bf16 would sum the
 // rounded values in half the instructions, but it does not issue while an
@@ -460,30 +470,30 @@ __device__ __forceinline__ float pack_sum(const f32x16& arg, bf16x8 (&pf)[2]) {
   return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-template <int D>
-__device__ __forceinline__ void softmax_pp(int lane, int valid, bool first, f32x16 (&sacc)[2][1],
-                                           bf16x8 (&pf)[2][2], f32x16 (&oacc)[2][D / 32], float (&m_used)[2],
-                                           float (&lsum)[2], const float (&c)[2]) {
+template <int D, int QB>
+__device__ __forceinline__ void softmax_pp(int valid, bool first, f32x16 (&sacc)[QB][1],
+                                           bf16x8 (&pf)[QB][2], f32x16 (&oacc)[QB][D / 32], float (&m_used)[QB],
+                                           float (&lsum)[QB], const float (&c)[QB]) {
   if (valid < 32) {  // keys past the range end score -inf (see tile_max)
-    const int lim = valid - 4 * (lane >> 5);
+    const int lim = valid - 4 * (fresh_lane() >> 5);
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         if (8 * (r >> 2) + (r & 3) >= lim) sacc[qb][0][r] = -INFINITY;
   }
   if (first) {
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) rescale<D>(oacc[qb], m_used[qb], lsum[qb], tile_max(lane, 32, sacc[qb], c[qb]));
+    for (int qb = 0; qb < QB; ++qb) rescale<D>(oacc[qb], m_used[qb], lsum[qb], tile_max(0, 32, sacc[qb], c[qb]));
   }
   // the arguments of both blocks first (independent), then one block at a
   // time, so that a block's arguments die at its check
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb)
+  for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[qb][0][r] = __builtin_fmaf(sacc[qb][0][r], c[qb], -m_used[qb]);
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
+  for (int qb = 0; qb < QB; ++qb) {
     float ts = pack_sum(sacc[qb][0], pf[qb]);
     if (__any(!(ts <= kSumLimit))) {
       float mx = 0.f;  // the shift: max(0, max a) over the row
@@ -615,7 +625,7 @@ __device__ __forceinline__ void tile_compute(const StageAddr<D>& sa, int lane, i
     if (j > 0 && valid <= j * SUB) break;
     f32x16 sacc[QB][KB];
     bf16x8 pf[QB][2 * KB];
-    s_part<D, QB>(src, j, qf, sacc);
+    s_part<D, QB, KB>(src, j, qf, sacc);
     softmax_part<D, QB>(lane, valid - j * SUB, sacc, pf, oacc, m_used, lsum, c);
     pv_part<D, QB>(src, j, pf, oacc);
   }
@@ -743,17 +753,6 @@ __device__ __forceinline__ void run_ring(const Params& p, const QSeg& qs, int b,
 // key masked, so that both groups pass the same barriers.
 constexpr int kLoaders = 4;  // waves of group 1
 
-// The lane index computed afresh (v_mbcnt over a full mask) where it is
-// needed: written as inline assembly so that the compiler neither hoists it
-// out of the tile loop nor keeps it live across the phases, where a register
-// is only to be had by spilling (a spilled lane index costs a scratch reload,
-// a full memory latency, in the phase that issues the tile loads).
-__device__ __forceinline__ int fresh_lane() {
-  int l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
-
 // Issue the loads of one K/V tile from the loader wave lw of group 1: its
 // instruction i fills the 1 KB chunk c = i * 4 + lw of each tensor, lane l
 // the granule position p = 64 c + l (row p / (D/8), swizzled slot).
@@ -815,40 +814,46 @@ __device__ __forceinline__ void pin_probs(bf16x8 (&pf)[QB][N], float (&m_used)[Q
 // 2 NB V^T fragments of sub-tile jv (O^T += V^T P^T), then the NDC K
 // fragments of sub-tile jk of ks (S^T = K Q^T), each read kPF fragments ahead
 // of its MFMAs, so that the first K reads are in flight during the last P V
-// MFMAs.  The first kPF V^T fragments arrive in a[] (v_prefetch), read at the
-// end of the softmax phase before, so that the phase's first MFMAs do not wait
-// for the LDS.
-template <int D>
-__device__ __forceinline__ void v_prefetch(const uint16_t* vs, const FragBase& fb, int jv, bf16x8 (&a)[4]) {
+// MFMAs.  The first kPPAhead V^T fragments arrive in a[] (v_prefetch), read at
+// the end of the softmax phase before, so that the phase's first MFMAs do not
+// wait for the LDS.  With one block a fragment feeds one MFMA, so more of them
+// are read ahead.
+template <int D, int QB>
+constexpr int kPPAhead = QB == 2 || D == 64 ? 3 : 7;
+
+template <int D, int QB>
+__device__ __forceinline__ void v_prefetch(const uint16_t* vs, const FragBase& fb, int jv,
+                                           bf16x8 (&a)[kPPAhead<D, QB> + 1]) {
   constexpr int NV = D / 16;  // 2 NB
 #pragma unroll
-  for (int f = 0; f < Blk<2>::kPF; ++f) a[f] = v_frag<D>(vs, fb, jv * NV + f);
+  for (int f = 0; f < kPPAhead<D, QB>; ++f) a[f] = v_frag<D>(vs, fb, jv * NV + f);
 }
 
-template <int D>
+template <int D, int QB>
 __device__ __forceinline__ void mfma_phase(const uint16_t* vs, const uint16_t* ks, const FragBase& fb, int jv, int jk,
-                                           bf16x8 (&a)[4], const bf16x8 (&pf)[2][2], const bf16x8 (&qf)[2][D / 16],
-                                           f32x16 (&oacc)[2][D / 32], f32x16 (&sacc)[2][1]) {
+                                           bf16x8 (&a)[kPPAhead<D, QB> + 1], const bf16x8 (&pf)[QB][2],
+                                           const bf16x8 (&qf)[QB][D / 16], f32x16 (&oacc)[QB][D / 32],
+                                           f32x16 (&sacc)[QB][1]) {
   constexpr int NB = D / 32, NDC = D / 16, NV = 2 * NB, NF = NV + NDC;
-  constexpr int PF = Blk<2>::kPF;
-  static_assert(PF + 1 == 4 && NV >= PF, "fragment ring of four");
+  constexpr int PF = kPPAhead<D, QB>, R = PF + 1;
+  static_assert(NV >= PF, "the fragments read ahead of the phase are V^T ones");
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     if (f < NV) {
       const int cc = f / NB, nb = f % NB;
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-        oacc[qb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f % 4], pf[qb][cc], oacc[qb][nb], 0, 0, 0);
+      for (int qb = 0; qb < QB; ++qb)
+        oacc[qb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f % R], pf[qb][cc], oacc[qb][nb], 0, 0, 0);
     } else {
       const int dc = f - NV;
 #pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-        sacc[qb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f % 4], qf[qb][dc], dc == 0 ? f32x16{} : sacc[qb][0],
+      for (int qb = 0; qb < QB; ++qb)
+        sacc[qb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[f % R], qf[qb][dc], dc == 0 ? f32x16{} : sacc[qb][0],
                                                               0, 0, 0);
     }
     const int g = f + PF;
-    if (g < NV) a[g % 4] = v_frag<D>(vs, fb, jv * NV + g);
-    else if (g < NF) a[g % 4] = k_frag<D>(ks, fb, jk * NDC + g - NV);
+    if (g < NV) a[g % R] = v_frag<D>(vs, fb, jv * NV + g);
+    else if (g < NF) a[g % R] = k_frag<D>(ks, fb, jk * NDC + g - NV);
     sched_fence();
   }
 }
@@ -937,14 +942,14 @@ __device__ __forceinline__ void widen_tile_pp(int lw, int slot, float sk, float 
 // S^T of sub-tile 0 of tile t + 1 in stage (S + 1) % 3).  A wave raises its issue
 // priority for its MFMA phases, so that the other wave's softmax instructions
 // fill the gaps between its MFMAs rather than delay them (measured 1-2.5%
-// faster than equal priorities or a raised softmax phase).  In the FP8 ring
-// each phase takes the lane index afresh (fresh_lane): with the widening's
-// registers it would otherwise be spilled and reloaded once per tile.
-template <int S, int D, bool kF8>
+// faster than equal priorities or a raised softmax phase).  At D = 128
+// each phase takes the lane index afresh (fresh_lane): it would otherwise be
+// spilled and reloaded once per tile.
+template <int S, int D, bool kF8, int QB>
 __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int grp, int lw, int lane,
-                                        const bf16x8 (&qf)[2][D / 16], f32x16 (&oacc)[2][D / 32],
-                                        float (&m_used)[2], float (&lsum)[2], const float (&c)[2],
-                                        f32x16 (&sacc)[2][1], bf16x8 (&pf)[2][2]) {
+                                        const bf16x8 (&qf)[QB][D / 16], f32x16 (&oacc)[QB][D / 32],
+                                        float (&m_used)[QB], float (&lsum)[QB], const float (&c)[QB],
+                                        f32x16 (&sacc)[QB][1], bf16x8 (&pf)[QB][2]) {
   constexpr int SN = (S + 1) % 3;  // stage of tile t + 1
   constexpr int SL = (S + 2) % 3;  // stage of tile t - 1, refilled with tile t + 2
   const int valid = tile_valid(st.ccur);
@@ -962,7 +967,7 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
     ++st.issued;
     if (t + 3 < st.n) cursor_next(p, st.icur);
   }
-  softmax_pp<D>(kF8 ? fresh_lane() : lane, valid, t == 0, sacc, pf, oacc, m_used, lsum, c);
+  softmax_pp<D, QB>(valid, t == 0, sacc, pf, oacc, m_used, lsum, c);
   pin_probs(pf, m_used, lsum);
   if constexpr (kF8) {
     // tile t + 2 (its codes landed; tile t + 3's may be in flight) widened into
@@ -977,20 +982,20 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
   // P V of sub-tile 2t, S^T of sub-tile 2t + 1; group 1 then waits for tile t + 1
   {
     sched_fence();
-    const FragBase fb = phase_base<D>(kF8 ? fresh_lane() : lane);
-    bf16x8 a[4];
-    v_prefetch<D>(vbuf<S>(), fb, 0, a);
+    const FragBase fb = phase_base<D>(kF8 && D == 128 ? fresh_lane() : lane);
+    bf16x8 a[kPPAhead<D, QB> + 1];
+    v_prefetch<D, QB>(vbuf<S>(), fb, 0, a);
     sched_fence();
     mfma_barrier();
     __builtin_amdgcn_s_setprio(3);
-    mfma_phase<D>(vbuf<S>(), kbuf<S>(), fb, 0, 1, a, pf, qf, oacc, sacc);
+    mfma_phase<D, QB>(vbuf<S>(), kbuf<S>(), fb, 0, 1, a, pf, qf, oacc, sacc);
     pin_scores(sacc);
   }
   if (!kF8 && grp == 1 && t + 1 < st.n) wait_tiles_pp<D>(st.issued - (t + 2));
   // softmax of sub-tile 2t + 1
   ring_barrier();
   __builtin_amdgcn_s_setprio(0);
-  softmax_pp<D>(kF8 ? fresh_lane() : lane, valid - 32, false, sacc, pf, oacc, m_used, lsum, c);
+  softmax_pp<D, QB>(valid - 32, false, sacc, pf, oacc, m_used, lsum, c);
   pin_probs(pf, m_used, lsum);
   // P V of sub-tile 2t + 1, S^T of the next tile's first sub-tile (after the
   // last tile it reads a stage that holds no new tile and the scores go
@@ -998,23 +1003,23 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
   // phase)
   {
     sched_fence();
-    const FragBase fb = phase_base<D>(kF8 ? fresh_lane() : lane);
-    bf16x8 a[4];
-    v_prefetch<D>(vbuf<S>(), fb, 1, a);
+    const FragBase fb = phase_base<D>(kF8 && D == 128 ? fresh_lane() : lane);
+    bf16x8 a[kPPAhead<D, QB> + 1];
+    v_prefetch<D, QB>(vbuf<S>(), fb, 1, a);
     sched_fence();
     mfma_barrier();
     __builtin_amdgcn_s_setprio(3);
-    mfma_phase<D>(vbuf<S>(), kbuf<SN>(), fb, 1, 0, a, pf, qf, oacc, sacc);
+    mfma_phase<D, QB>(vbuf<S>(), kbuf<SN>(), fb, 1, 0, a, pf, qf, oacc, sacc);
     pin_scores(sacc);
   }
   if (t + 1 < st.n) cursor_next(p, st.ccur);
 }
 
-template <int D, bool kF8 = false>
+template <int D, bool kF8, int QB>
 __device__ __forceinline__ void run_ring_pp(const Params& p, const QSeg& qs, int b, int h, int kt_begin, int kt_end,
-                                            int wave, int lane, const bf16x8 (&qf)[2][D / 16],
-                                            f32x16 (&oacc)[2][D / 32], float (&m_used)[2], float (&lsum)[2],
-                                            const float (&c)[2], float sk = 1.f, float sv = 1.f) {
+                                            int wave, int lane, const bf16x8 (&qf)[QB][D / 16],
+                                            f32x16 (&oacc)[QB][D / 32], float (&m_used)[QB], float (&lsum)[QB],
+                                            const float (&c)[QB], float sk = 1.f, float sv = 1.f) {
   const int n = kt_end - kt_begin;  // the same for every wave of the work-group
   if (n <= 0) return;
   const int grp = wave >> 2, lw = wave & 3;
@@ -1065,16 +1070,16 @@ __device__ __forceinline__ void run_ring_pp(const Params& p, const QSeg& qs, int
   }
   ring_barrier();
   if (grp == 1) ring_barrier();  // group 1 runs one phase behind group 0
-  f32x16 sacc[2][1];
-  bf16x8 pf[2][2];
-  s_part<D, 2>(PtrFrags<D>{kbuf<0>(), vbuf<0>(), phase_base<D>(lane)}, 0, qf, sacc);
+  f32x16 sacc[QB][1];
+  bf16x8 pf[QB][2];
+  s_part<D, QB, 1>(PtrFrags<D>{kbuf<0>(), vbuf<0>(), phase_base<D>(lane)}, 0, qf, sacc);
   pin_scores(sacc);
   for (int t = 0; t < n; t += 3) {
-    pp_tile<0, D, kF8>(p, t, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
+    pp_tile<0, D, kF8, QB>(p, t, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
     if (t + 1 >= n) break;
-    pp_tile<1, D, kF8>(p, t + 1, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
+    pp_tile<1, D, kF8, QB>(p, t + 1, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
     if (t + 2 >= n) break;
-    pp_tile<2, D, kF8>(p, t + 2, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
+    pp_tile<2, D, kF8, QB>(p, t + 2, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
   }
   if (grp == 0) ring_barrier();  // the barrier group 1 passed at the start
 }
@@ -1088,14 +1093,16 @@ __device__ __forceinline__ int xcd_logical_block(int bid, int nblk) {
   return (xcd < rem) ? xcd * (per + 1) + kx : rem * (per + 1) + (xcd - rem) * per + kx;
 }
 
-// One query tile t of segment qs, batch b, head h, over the segment's key
-// tiles [kt_begin, kt_end).  part_row < 0: final output (bf16 O and LSE);
-// otherwise unnormalised fp32 partials (O, running max in log2 units, row
-// sum) at workspace row part_row + (row inside the tile).  Wave w owns rows
-// w * 32 QB .. + 32 QB - 1 of the tile, block qb of it rows
-// w * 32 QB + 32 qb + lane % 32.
-template <int D, bool kF8, int QB>
-__device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int t, int b, int h, int kt_begin,
+// The query tile of rows seg_row0 .. of segment qs, batch b, head h, over the
+// segment's key tiles [kt_begin, kt_end).  part_row < 0: final output (bf16 O
+// and LSE); otherwise unnormalised fp32 partials (O, running max in log2
+// units, row sum) at workspace row part_row + (row inside the tile).  Wave w
+// owns rows w * 32 QB .. + 32 QB - 1 of the tile, block qb of it rows
+// w * 32 QB + 32 qb + lane % 32.  kPingPong: the ping-pong ring (either block
+// count: a row's bits are the same in both, since a 32-row block's arithmetic
+// does not depend on the other block).
+template <int D, bool kF8, int QB, bool kPingPong>
+__device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int seg_row0, int b, int h, int kt_begin,
                                             int kt_end, int64_t part_row, int wave, int lane) {
   constexpr int GR = D / 8;
   constexpr int NDC = D / 16;  // 16-wide d chunks of the QK^T contraction
@@ -1103,12 +1110,10 @@ __device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int
   constexpr int kLoads = kBN * GR / kThreads;
   constexpr int BM = Blk<QB>::kRows;
   constexpr int RW = 32 * QB;  // query rows per wave
-  constexpr bool kPingPong = QB == 2;
   static_assert(kLoads >= 1 && kBN * GR % kThreads == 0, "tile granules must divide over the threads");
   static_assert(!kPingPong || kWaves == 2 * kLoaders, "ping-pong pairs waves w and w + 4 on one SIMD");
   const int hh = lane >> 5;  // which 32-lane half
 
-  const int seg_row0 = (t - qs.tile0) * BM;
   const int rows_valid = min(BM, qs.len - seg_row0);
   const int row0 = qs.row0 + seg_row0;  // first row of the tile in the Q/O buffers
   const bool wave_active = wave * RW < rows_valid;  // wave-uniform
@@ -1159,15 +1164,15 @@ __device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int
       int kt_split = 0;
       for (int r = qs.r0; r < qs.r0 + qs.nr && p.range[r].src == 0; ++r) kt_split += p.range[r].ntiles;
       const int mid = min(max(kt_split, kt_begin), kt_end);
-      run_ring_pp<D>(p, qs, b, h, kt_begin, mid, wave, lane, qf, oacc, m_used, lsum, cb);
+      run_ring_pp<D, false, QB>(p, qs, b, h, kt_begin, mid, wave, lane, qf, oacc, m_used, lsum, cb);
       if (mid < kt_end) {
         if (kt_begin < mid) ring_barrier();  // the first ring's stages are read no more
         const float sk = p.kv_scale[(int64_t(b) * p.H + h) * 2];
         const float sv = p.kv_scale[(int64_t(b) * p.H + h) * 2 + 1];
-        run_ring_pp<D, true>(p, qs, b, h, mid, kt_end, wave, lane, qf, oacc, m_used, lsum, cb, sk, sv);
+        run_ring_pp<D, true, QB>(p, qs, b, h, mid, kt_end, wave, lane, qf, oacc, m_used, lsum, cb, sk, sv);
       }
     } else {
-      run_ring_pp<D>(p, qs, b, h, kt_begin, kt_end, wave, lane, qf, oacc, m_used, lsum, cb);
+      run_ring_pp<D, false, QB>(p, qs, b, h, kt_begin, kt_end, wave, lane, qf, oacc, m_used, lsum, cb);
     }
   } else {
     // per-lane byte offsets of this lane's granules inside a tile, per key source
@@ -1184,44 +1189,49 @@ __device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int
     run_ring<D, QB>(p, qs, b, h, kt_begin, kt_end, wave, lane, wave_active, voff0, voff1, qf, oacc, m_used, lsum, cb);
   }
 
-  // ---- epilogue (the half-sum exchange runs on every lane before any lane leaves)
+  // ---- epilogue (the half-sum exchange runs on every lane before any lane
+  // leaves).  The lane's rows are computed afresh: none of it lives across the
+  // key loop, where the two-block tile has no register to spare.
+  const int el = kPingPong ? fresh_lane() : lane, ehh = el >> 5;
+  const int e_valid = min(BM, qs.len - seg_row0);
   float l_tot[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) l_tot[qb] = sum_halves(lsum[qb]);
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    if (!row_ok[qb]) continue;
+    const int er = wave * RW + 32 * qb + (el & 31);  // row inside the tile
+    if (er >= e_valid) continue;
     if (part_row >= 0) {
-      const int64_t prow = part_row + my_row[qb];
+      const int64_t prow = part_row + er;
       float* op = p.ws_o + prow * D;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = nb * 32 + 8 * q4 + 4 * hh;
+          const int d = nb * 32 + 8 * q4 + 4 * ehh;
           float4 v4 = make_float4(oacc[qb][nb][4 * q4], oacc[qb][nb][4 * q4 + 1], oacc[qb][nb][4 * q4 + 2],
                                   oacc[qb][nb][4 * q4 + 3]);
           *reinterpret_cast<float4*>(op + d) = v4;
         }
-      if (hh == 0) {
+      if (ehh == 0) {
         p.ws_ml[prow * 2] = m_used[qb];
         p.ws_ml[prow * 2 + 1] = l_tot[qb];
       }
     } else {
-      const int grow = row0 + my_row[qb];
+      const int grow = qs.row0 + seg_row0 + er;
       const float inv = l_tot[qb] > 0.f ? 1.f / l_tot[qb] : 0.f;
       uint16_t* op = p.o + int64_t(b) * p.o_sb + int64_t(grow) * p.o_st + int64_t(h) * D;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = nb * 32 + 8 * q4 + 4 * hh;
+          const int d = nb * 32 + 8 * q4 + 4 * ehh;
           __bf16 o4[4];
 #pragma unroll
           for (int j = 0; j < 4; ++j) o4[j] = (__bf16)(oacc[qb][nb][4 * q4 + j] * inv);
           *reinterpret_cast<u32x2*>(op + d) = __builtin_bit_cast(u32x2, o4);
         }
-      if (p.lse && hh == 0)
+      if (p.lse && ehh == 0)
         p.lse[(int64_t(b) * p.H + h) * p.n_rows + grow] =
             l_tot[qb] > 0.f ? m_used[qb] * 0.69314718055994531f + __logf(l_tot[qb]) : -INFINITY;
     }
@@ -1278,11 +1288,17 @@ __device__ __forceinline__ void copy_tail(const CopyTail& c, int j, int tid) {
 
 // One work-group per (batch, head, query tile, key split), then p.cp.blocks
 // copy work-groups (the prefill's cache store; unsplit bf16 launches only).
-// The host plans the query tiles with p.bm = rows_per_wg of the kernel's
-// block count.
+// The host plans query tiles of p.bm = rows_per_wg(kQBPlain) = 512 rows.
+//
+// A tile, or what is left of one, of at most 256 rows runs with one 32-row
+// block per wave: 0.6 (D = 128) or 0.65 (D = 64) of a whole tile's time, since
+// every K and V^T fragment then feeds one MFMA and the fragment reads take as
+// many LDS cycles as the MFMAs.  The last p.half_tiles tiles run as two
+// work-groups of 256 rows each, on CUs that would be idle (half_tiles()).
 template <int D, bool kSplit, bool kF8>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
-  constexpr int QB = kF8 ? kQBFp8 : kQBPlain;
+  static_assert(kQBFp8 == kQBPlain, "one tile size over either cache");
+  constexpr int BM = rows_per_wg(kQBPlain);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int n_attn = gridDim.x;
@@ -1293,19 +1309,24 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
       return;
     }
   }
-  int split, rest;
+  int split, rest, half = -1;  // half: which 256 rows of the tile, -1 for all
+  int lr_tile = 0;             // last-round split: index among its tiles
   if (kSplit && p.lr_tiles > 0) {
     // last-round split: blocks [0, U) are whole query tiles (logical tiles
     // [0, U)), then the long pieces of logical tiles [U, U + T), then their
-    // short pieces, which the CUs idle in the last round take first
-    const int T = p.lr_tiles, U = n_attn - 2 * T;
+    // short pieces, which the CUs idle in the last round take first; each
+    // piece is one work-group or two of half the rows
+    const int halves = p.half_tiles > 0 ? 2 : 1, n = p.lr_tiles * halves, U = n_attn - 2 * n;
     if (int(blockIdx.x) < U) {
       split = -1;
       rest = xcd_logical_block(blockIdx.x, U);
     } else {
       const int i = blockIdx.x - U;
-      split = i >= T;
-      rest = U + xcd_logical_block(i - split * T, T);
+      split = i >= n;
+      const int j = xcd_logical_block(i - split * n, n);
+      lr_tile = j / halves;
+      if (halves == 2) half = j & 1;
+      rest = U + lr_tile;
     }
   } else if (kSplit && p.tail_num > 0) {
     // tail split: blocks [0, Q) are the long pieces, dispatched first; blocks
@@ -1315,12 +1336,21 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
     const int q = n_attn / 2;
     split = blockIdx.x >= q;
     rest = xcd_logical_block(blockIdx.x - split * q, q);
-  } else {
+  } else if (kSplit) {
     const int w = xcd_logical_block(blockIdx.x, n_attn);
     split = w % p.splits;
     rest = w / p.splits;
+  } else {
+    split = 0;
+    const int U = n_attn - 2 * p.half_tiles;
+    if (int(blockIdx.x) < U) {
+      rest = xcd_logical_block(blockIdx.x, U);
+    } else {
+      const int j = xcd_logical_block(blockIdx.x - U, 2 * p.half_tiles);
+      rest = U + j / 2;
+      half = j & 1;
+    }
   }
-  const int w = rest;  // logical query tile
   const int t = rest % p.n_qtiles;
   rest /= p.n_qtiles;
   const int h = rest % p.H, b = rest / p.H;
@@ -1328,12 +1358,17 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
   int qi = 0;
   while (qi + 1 < p.n_qseg && p.qseg[qi + 1].tile0 <= t) ++qi;
   const QSeg qs = p.qseg[qi];
-  int kt_begin, kt_end;
+  int seg_row0 = (t - qs.tile0) * BM;
+  if (half > 0) {
+    seg_row0 += BM / 2;
+    if (seg_row0 >= qs.len) return;
+  }
+  int kt_begin = 0, kt_end = qs.ktiles;
   if (kSplit && p.tail_num > 0) {
     const int mid = int((int64_t(qs.ktiles) * p.tail_num) >> 10);
     kt_begin = split > 0 ? mid : 0;
     kt_end = split == 0 ? mid : qs.ktiles;
-  } else {
+  } else if (kSplit) {
     kt_begin = int(int64_t(qs.ktiles) * split / p.splits);
     kt_end = int(int64_t(qs.ktiles) * (split + 1) / p.splits);
   }
@@ -1341,12 +1376,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
   if constexpr (kSplit) {
     if (p.lr_tiles > 0) {
       // piece s of last-round tile i: workspace rows (s T + i) BM + row
-      if (split >= 0) part_row = (int64_t(split) * p.lr_tiles + (w - (n_attn - 2 * p.lr_tiles))) * Blk<QB>::kRows;
+      if (split >= 0) part_row = (int64_t(split) * p.lr_tiles + lr_tile) * BM + (half > 0 ? BM / 2 : 0);
     } else {
-      part_row = ((int64_t(split) * p.B + b) * p.H + h) * p.n_rows + qs.row0 + (t - qs.tile0) * Blk<QB>::kRows;
+      part_row = ((int64_t(split) * p.B + b) * p.H + h) * p.n_rows + qs.row0 + seg_row0;
     }
   }
-  attend_tile<D, kF8, QB>(p, qs, t, b, h, kt_begin, kt_end, part_row, wave, lane);
+  if (half >= 0 || qs.len - seg_row0 <= BM / 2)
+    attend_tile<D, kF8, 1, true>(p, qs, seg_row0, b, h, kt_begin, kt_end, part_row, wave, lane);
+  else
+    attend_tile<D, kF8, 2, true>(p, qs, seg_row0, b, h, kt_begin, kt_end, part_row, wave, lane);
 }
 
 // Balanced schedule: work-group g of G takes the key-tile units
@@ -1377,7 +1415,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_balanced_kernel(const Pa
     const bool whole = kt0 == 0 && kt1 == qs.ktiles;
     const int64_t part_row = whole ? -1 : int64_t(first ? 2 * g : 2 * g + 1) * Blk<QB>::kRows;
     if (!first) ring_barrier();  // every wave is done with the previous piece's LDS stages
-    attend_tile<D, kF8, QB>(p, qs, qs.tile0 + tl, int(bh / p.H), int(bh % p.H), kt0, kt1, part_row, wave, lane);
+    attend_tile<D, kF8, QB, false>(p, qs, tl * Blk<QB>::kRows, int(bh / p.H), int(bh % p.H), kt0, kt1, part_row, wave, lane);
     u += kt1 - kt0;
     first = false;
   }
@@ -1577,13 +1615,18 @@ int scratch_address(void** ptr) {
 }
 
 int launch_attention(const Params& p, int D, void* stream) {
-  const int64_t per_batch = int64_t(p.H) * p.n_qtiles * p.splits;
-  // the last-round split adds one short piece per split tile
-  const int64_t blocks =
-      p.lr_tiles > 0 ? int64_t(p.B) * p.H * p.n_qtiles + p.lr_tiles : int64_t(p.B) * per_batch;
+  const int64_t tiles = int64_t(p.B) * p.H * p.n_qtiles;
+  // the last-round split adds one short piece per split tile; a tile (or
+  // piece) run as two halves adds one work-group
+  const int64_t blocks = p.lr_tiles > 0 ? tiles + p.lr_tiles + (p.half_tiles > 0 ? 2 * int64_t(p.lr_tiles) : 0)
+                                        : tiles * p.splits + p.half_tiles;
   if (blocks == 0) return 0;
-  if (p.lr_tiles < 0 ||
-      (p.lr_tiles > 0 && (p.splits != 2 || p.tail_num <= 0 || p.lr_tiles > int64_t(p.B) * p.H * p.n_qtiles)))
+  if (p.lr_tiles < 0 || (p.lr_tiles > 0 && (p.splits != 2 || p.tail_num <= 0 || p.lr_tiles > tiles)))
+    return int(hipErrorInvalidValue);
+  // halves are the last tiles of an unsplit grid or all tiles of a last-round
+  // split
+  if (p.half_tiles < 0 || p.half_tiles > tiles ||
+      (p.half_tiles > 0 && (p.lr_tiles > 0 ? p.half_tiles != p.lr_tiles : p.splits != 1 || per_batch_launches(p))))
     return int(hipErrorInvalidValue);
   // copy work-groups ride on unsplit bf16 grids only (the other kernels have
   // no copy path)
@@ -1613,7 +1656,7 @@ int launch_attention(const Params& p, int D, void* stream) {
         q.src[i].v = p.src[i].v ? p.src[i].v + int64_t(b) * p.src[i].v_sb : nullptr;
       }
       q.kv_scale = p.kv_scale ? p.kv_scale + int64_t(b) * p.H * 2 : nullptr;
-      launch(q, per_batch);
+      launch(q, tiles / p.B);
     }
   } else {
     launch(p, blocks);

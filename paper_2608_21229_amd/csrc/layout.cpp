@@ -363,6 +363,23 @@ int32_t last_round_tiles(Params& p) {
   return int32_t(T);
 }
 
+int32_t half_tiles(const Params& p) {
+  // A tile in two work-groups of 256 rows takes 0.6 (D = 128) or 0.65 (D = 64)
+  // of a whole one's time on a full chip, 0.83 and 0.75 where the other half
+  // of the CUs was idle before (the clock falls), so it pays only where every
+  // extra work-group finds an idle CU.  The last-round split's two pieces of
+  // T <= 64 tiles: five references of 4096, 32 heads (T = 32) 1 229 -> 1 141
+  // us; T = 64 at D = 64 553 -> 510 us.  A whole unsplit grid of at most 128:
+  // 128 tiles of 256 key tiles 650 -> 537 us (D = 64 513 -> 390 us).  The last
+  // partial round of an unsplit grid, whose idle CUs the prefill's copy
+  // work-groups use, measured no better or slower (1 024-token references
+  // among 4 096: 642 -> 639-700 us).
+  if (p.lr_tiles > 0) return 4 * p.lr_tiles <= kCUs ? p.lr_tiles : 0;
+  if (p.splits != 1) return 0;
+  const int64_t A = int64_t(p.B) * p.H * p.n_qtiles;
+  return 2 * A + p.cp.blocks <= kCUs ? int32_t(A) : 0;
+}
+
 int32_t tail_num(const Params& p) {
   // Q query tiles on Q CUs; 256 - Q CUs run the short pieces, R rounds each:
   // the long piece takes R / (R + 1) of the keys so both end together.

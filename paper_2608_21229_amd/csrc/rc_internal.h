@@ -99,6 +99,8 @@ struct Params {
   int32_t tail_num;    // tail split (splits = 2): split 0 takes floor(ktiles * tail_num / 1024) key tiles; 0 = even
   int32_t lr_tiles;    // last-round split (splits = 2, tail_num > 0): only the last lr_tiles query tiles
                        // (logical order) run as a long and a short piece; the others whole, written directly
+  int32_t half_tiles;  // unsplit grid: the last half_tiles query tiles (logical order) run as two work-groups of
+                       // half the rows; last-round split: lr_tiles when its pieces do, else 0
   int32_t fp8;         // key source 1 is the FP8 cache
   const float* kv_scale;  // FP8 cache: [B, H, 2] power-of-two scales of K and V
   int64_t units_bh;    // key-tile units (query tile x key tile) per (batch, head)
@@ -176,6 +178,9 @@ int32_t tail_num(const Params& p);  // the long split's share of the key tiles, 
 // The full recompute's last-round split: the query tiles of an unsplit grid's
 // partial last round (0 when none pays), with p.tail_num set for them.
 int32_t last_round_tiles(Params& p);
+// How many of the last query tiles run as two work-groups of half the rows
+// (p.half_tiles), once splits, lr_tiles and cp.blocks are set.
+int32_t half_tiles(const Params& p);
 // The prefill's bf16 cache store: the copy work-groups appended to the
 // attention grid and the flat cache rows [0, rows) they take; the store
 // kernel copies the rest.

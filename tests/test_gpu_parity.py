@@ -507,3 +507,42 @@ def test_step_query_segment_without_keys(splits):
     check(ol, Ol, f"no-key segment step splits={splits} O")
     check_lse(lsel, Ll, f"no-key segment step splits={splits}")
     assert bool((ol[:, :300] == 0).all()) and bool(torch.isinf(lsel[:, :, :300]).all())
+
+
+@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (64, True), (128, True)])
+@pytest.mark.parametrize("lens", [(300, 600), (256, 513), (1, 257)])
+def test_half_tiles_match_whole_tiles(lens, D, fp8):
+    """A grid of at most 128 query tiles runs every tile as two work-groups of
+    256 rows, and rows past a tile's first 256 may be few or none; a larger
+    grid runs whole tiles.  A head's rows are the same bits in both (the same
+    MFMA chains), against the oracle on sampled rows."""
+    from synthgen import Workload
+    lt, x = lens
+    segs = ((0, 24), (1, lt), (2, x), (3, 200), (3, 90))
+    wl = Workload("halves", 1, 80, D, segs, std=1.0, seed=31)
+    print(f"[case] half tiles lens={lens} D={D} fp8={fp8}", flush=True)
+    inp = draw_inputs(wl)
+    L = layout_for(inp, "perref")
+
+    def run(h0, h1):
+        st = [t[:, :, h0:h1].contiguous().to(DEV) for t in inp.static]
+        lv = [t[:, :, h0:h1].contiguous().to(DEV) for t in inp.live]
+        if fp8:
+            o, _, k8, v8, sc = rc.ref_kv_prefill_fp8(L, *st, scale=wl.scale)
+            ol, lse = rc.step_masked_attention_fp8(L, *lv, k8, v8, sc, splits=1, scale=wl.scale, want_lse=True)
+        else:
+            o, _, kc, vc = rc.ref_kv_prefill(L, *st, scale=wl.scale)
+            ol, lse = rc.step_masked_attention(L, *lv, kc, vc, splits=1, scale=wl.scale, want_lse=True)
+        torch.cuda.synchronize()
+        return o, ol, lse
+
+    whole = run(0, 80)
+    half = run(3, 7)
+    for a, b, d in ((whole[0], half[0], 2), (whole[1], half[1], 2), (whole[2], half[2], 1)):
+        assert torch.equal(a.narrow(d, 3, 4), b)
+    if not fp8:
+        rows = sample_rows(lt + x, 7, seed=2)
+        k, v = (inp.static[i].permute(0, 2, 1, 3) for i in (1, 2))
+        O, _, _ = oa.denoise_step(inp.kinds, inp.lens, om.perref_mask(inp.kinds), *(f64(t) for t in inp.live), f64(k),
+                                  f64(v), wl.scale, rows=rows)
+        check(whole[1], O, f"half tiles {lens} D={D}", rows)
