@@ -168,17 +168,22 @@ __shared__ __attribute__((aligned(1024))) uint16_t g_v1[kTileElems];
 __shared__ __attribute__((aligned(1024))) uint16_t g_k2[kTileElems];  // third stage: ping-pong ring only
 __shared__ __attribute__((aligned(1024))) uint16_t g_v2[kTileElems];
 
+__shared__ __attribute__((aligned(1024))) uint16_t g_k3[kBN * 64];  // fourth stage: 64-wide heads only
+__shared__ __attribute__((aligned(1024))) uint16_t g_v3[kBN * 64];
+
 template <int S>
 __device__ __forceinline__ uint16_t* kbuf() {
   if constexpr (S == 0) return g_k0;
   else if constexpr (S == 1) return g_k1;
-  else return g_k2;
+  else if constexpr (S == 2) return g_k2;
+  else return g_k3;
 }
 template <int S>
 __device__ __forceinline__ uint16_t* vbuf() {
   if constexpr (S == 0) return g_v0;
   else if constexpr (S == 1) return g_v1;
-  else return g_v2;
+  else if constexpr (S == 2) return g_v2;
+  else return g_v3;
 }
 
 // Work-group barrier without the memory fences of __syncthreads(): every
@@ -753,6 +758,24 @@ __device__ __forceinline__ void run_ring(const Params& p, const QSeg& qs, int b,
 // key masked, so that both groups pass the same barriers.
 constexpr int kLoaders = 4;  // waves of group 1
 
+// At D = 64 a tile's MFMAs take 2 048 cycles of a SIMD and its softmax work
+// about as many issue slots again, in phases more than twice as long as the
+// MFMA phases: with a barrier per phase the matrix unit and, since one wave
+// alone issues a VALU instruction every 5 cycles where two share one every
+// 2.5, the VALU both wait.  So there the waves run free between one barrier
+// per tile: group 0 passes it at its tile's start, group 1 before its last
+// MFMA phase of the tile before (the same offset of one phase).  After the
+// barrier of tile t group 0 has read all of tile t - 1 and group 1 may still
+// read it, tiles t and t + 1 have landed, and tile t + 2 loads: four stages.
+// Group 1 waits for tile t + 2 at the end of its second softmax of tile t.
+// (256 whole tiles of 256 key tiles on 256 CUs 557 -> 541 us, 128 of them in
+// halves 390 -> 332 us, the 40-head ragged step 515 -> 487 us.  At D = 128,
+// where the MFMA phases are the longer ones, the same scheme was 2% slower.)
+template <int D>
+constexpr bool kFreeRun = D == 64;
+template <int D>
+constexpr int kPPStages = kFreeRun<D> ? 4 : 3;
+
 // Issue the loads of one K/V tile from the loader wave lw of group 1: its
 // instruction i fills the 1 KB chunk c = i * 4 + lw of each tensor, lane l
 // the granule position p = 64 c + l (row p / (D/8), swizzled slot).
@@ -939,7 +962,7 @@ __device__ __forceinline__ void widen_tile_pp(int lw, int slot, float sk, float 
 
 // The four phases of tile t (stage S): softmax of sub-tile 2t, MFMA phase
 // (P V of 2t, S^T of 2t + 1), softmax of 2t + 1, MFMA phase (P V of 2t + 1,
-// S^T of sub-tile 0 of tile t + 1 in stage (S + 1) % 3).  A wave raises its issue
+// S^T of sub-tile 0 of tile t + 1 in the next stage).  A wave raises its issue
 // priority for its MFMA phases, so that the other wave's softmax instructions
 // fill the gaps between its MFMAs rather than delay them (measured 1-2.5%
 // faster than equal priorities or a raised softmax phase).  At D = 128
@@ -950,11 +973,13 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
                                         const bf16x8 (&qf)[QB][D / 16], f32x16 (&oacc)[QB][D / 32],
                                         float (&m_used)[QB], float (&lsum)[QB], const float (&c)[QB],
                                         f32x16 (&sacc)[QB][1], bf16x8 (&pf)[QB][2]) {
-  constexpr int SN = (S + 1) % 3;  // stage of tile t + 1
-  constexpr int SL = (S + 2) % 3;  // stage of tile t - 1, refilled with tile t + 2
+  constexpr bool kFree = kFreeRun<D>;
+  constexpr int SN = (S + 1) % kPPStages<D>;  // stage of tile t + 1
+  constexpr int SL = (S + 2) % kPPStages<D>;  // stage that tile t + 2 goes to
   const int valid = tile_valid(st.ccur);
   // softmax of sub-tile 2t; group 1 loads tile t + 2
-  ring_barrier();
+  if (!kFree || grp == 0) ring_barrier();
+  sched_fence();
   __builtin_amdgcn_s_setprio(0);
   if constexpr (kF8) {
     // the codes of tile t + 3 into the slot tile t + 1 left
@@ -962,7 +987,7 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
       issue_tile8_pp<D>(st.icur, lw, (t + 3) & 1);
       if (t + 4 < st.n) cursor_next(p, st.icur);
     }
-  } else if (grp == 1 && t >= 1 && t + 2 < st.n) {
+  } else if (grp == 1 && (kFree || t >= 1) && t + 2 < st.n) {
     issue_tile_pp<D>(st.icur, lw, kbuf<SL>(), vbuf<SL>());
     ++st.issued;
     if (t + 3 < st.n) cursor_next(p, st.icur);
@@ -986,17 +1011,19 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
     bf16x8 a[kPPAhead<D, QB> + 1];
     v_prefetch<D, QB>(vbuf<S>(), fb, 0, a);
     sched_fence();
-    mfma_barrier();
+    if (!kFree) mfma_barrier();
     __builtin_amdgcn_s_setprio(3);
     mfma_phase<D, QB>(vbuf<S>(), kbuf<S>(), fb, 0, 1, a, pf, qf, oacc, sacc);
     pin_scores(sacc);
   }
-  if (!kF8 && grp == 1 && t + 1 < st.n) wait_tiles_pp<D>(st.issued - (t + 2));
+  if (!kFree && !kF8 && grp == 1 && t + 1 < st.n) wait_tiles_pp<D>(st.issued - (t + 2));
   // softmax of sub-tile 2t + 1
-  ring_barrier();
+  if (!kFree) ring_barrier();
+  sched_fence();
   __builtin_amdgcn_s_setprio(0);
   softmax_pp<D, QB>(valid - 32, false, sacc, pf, oacc, m_used, lsum, c);
   pin_probs(pf, m_used, lsum);
+  if (kFree && !kF8 && grp == 1) wait_tiles_pp<D>(0);  // tile t + 2 landed
   // P V of sub-tile 2t + 1, S^T of the next tile's first sub-tile (after the
   // last tile it reads a stage that holds no new tile and the scores go
   // unused; computing it anyway keeps the old scores from living across this
@@ -1007,7 +1034,12 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
     bf16x8 a[kPPAhead<D, QB> + 1];
     v_prefetch<D, QB>(vbuf<S>(), fb, 1, a);
     sched_fence();
-    mfma_barrier();
+    if (!kFree) {
+      mfma_barrier();
+    } else if (grp == 1) {
+      if (kF8) ring_barrier();  // the widened tile's LDS writes are done
+      else mfma_barrier();
+    }
     __builtin_amdgcn_s_setprio(3);
     mfma_phase<D, QB>(vbuf<S>(), kbuf<SN>(), fb, 1, 0, a, pf, qf, oacc, sacc);
     pin_scores(sacc);
@@ -1061,12 +1093,14 @@ __device__ __forceinline__ void run_ring_pp(const Params& p, const QSeg& qs, int
       st.issued = 2;
       if (n > 2) {
         cursor_next(p, st.icur);
-        issue_tile_pp<D>(st.icur, lw, kbuf<2>(), vbuf<2>());
-        st.issued = 3;
-        if (n > 3) cursor_next(p, st.icur);
+        if (!kFreeRun<D>) {
+          issue_tile_pp<D>(st.icur, lw, kbuf<2>(), vbuf<2>());
+          st.issued = 3;
+          if (n > 3) cursor_next(p, st.icur);
+        }
       }
     }
-    wait_tiles_pp<D>(st.issued - 1);  // tile 0 landed
+    wait_tiles_pp<D>(kFreeRun<D> ? 0 : st.issued - 1);  // tile 0 (free-running: and tile 1) landed
   }
   ring_barrier();
   if (grp == 1) ring_barrier();  // group 1 runs one phase behind group 0
@@ -1074,12 +1108,16 @@ __device__ __forceinline__ void run_ring_pp(const Params& p, const QSeg& qs, int
   bf16x8 pf[QB][2];
   s_part<D, QB, 1>(PtrFrags<D>{kbuf<0>(), vbuf<0>(), phase_base<D>(lane)}, 0, qf, sacc);
   pin_scores(sacc);
-  for (int t = 0; t < n; t += 3) {
+  for (int t = 0; t < n; t += kPPStages<D>) {
     pp_tile<0, D, kF8, QB>(p, t, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
     if (t + 1 >= n) break;
     pp_tile<1, D, kF8, QB>(p, t + 1, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
     if (t + 2 >= n) break;
     pp_tile<2, D, kF8, QB>(p, t + 2, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
+    if constexpr (kPPStages<D> == 4) {
+      if (t + 3 >= n) break;
+      pp_tile<3, D, kF8, QB>(p, t + 3, st, grp, lw, lane, qf, oacc, m_used, lsum, c, sacc, pf);
+    }
   }
   if (grp == 0) ring_barrier();  // the barrier group 1 passed at the start
 }
@@ -1291,7 +1329,7 @@ __device__ __forceinline__ void copy_tail(const CopyTail& c, int j, int tid) {
 // The host plans query tiles of p.bm = rows_per_wg(kQBPlain) = 512 rows.
 //
 // A tile, or what is left of one, of at most 256 rows runs with one 32-row
-// block per wave: 0.6 (D = 128) or 0.65 (D = 64) of a whole tile's time, since
+// block per wave: 0.6 of a whole tile's time, since
 // every K and V^T fragment then feeds one MFMA and the fragment reads take as
 // many LDS cycles as the MFMAs.  The last p.half_tiles tiles run as two
 // work-groups of 256 rows each, on CUs that would be idle (half_tiles()).

@@ -364,13 +364,13 @@ int32_t last_round_tiles(Params& p) {
 }
 
 int32_t half_tiles(const Params& p) {
-  // A tile in two work-groups of 256 rows takes 0.6 (D = 128) or 0.65 (D = 64)
-  // of a whole one's time on a full chip, 0.83 and 0.75 where the other half
-  // of the CUs was idle before (the clock falls), so it pays only where every
+  // A tile in two work-groups of 256 rows takes 0.6 (either head_dim)
+  // of a whole one's time each on a full chip, 0.83 (D = 128) and 0.7 (D = 64)
+  // where the other half of the CUs was idle before (the clock falls), so it pays only where every
   // extra work-group finds an idle CU.  The last-round split's two pieces of
   // T <= 64 tiles: five references of 4096, 32 heads (T = 32) 1 229 -> 1 141
-  // us; T = 64 at D = 64 553 -> 510 us.  A whole unsplit grid of at most 128:
-  // 128 tiles of 256 key tiles 650 -> 537 us (D = 64 513 -> 390 us).  The last
+  // us; T = 64 at D = 64 542 -> 483 us.  A whole unsplit grid of at most 128:
+  // 128 tiles of 256 key tiles 650 -> 537 us (D = 64 482 -> 332 us).  The last
   // partial round of an unsplit grid, whose idle CUs the prefill's copy
   // work-groups use, measured no better or slower (1 024-token references
   // among 4 096: 642 -> 639-700 us).
