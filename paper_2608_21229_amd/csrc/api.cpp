@@ -383,8 +383,13 @@ rc_status step_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, float s
     c.D = D;
     c.n_rows = int32_t(n_live);
     c.splits = p.splits;
+    for (int i = 0; i < p.n_qseg; ++i) {
+      c.seg[c.n_seg++] = CombineParams::Seg{p.qseg[i].row0, p.qseg[i].len, c.n_blocks};
+      c.n_blocks += (p.qseg[i].len + 31) / 32;
+    }
   }
-  // combine: one thread per 4 output elements, 256 per work-group
+  // combine: one wave per (up to) 32 rows and 32 columns, four per work-group;
+  // fewer than 2^31 by this check and the attention grid's
   if (p.splits > 1) RC_TRY(check_blocks((int64_t(B) * H * n_live * (D / 4) + 255) / 256, "split-KV combine"));
   if (p.lr_tiles > 0) RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + p.lr_tiles, "step attention"));
   RC_TRY(hip_status(launch_attention(p, D, stream), "step attention launch"));

@@ -1131,6 +1131,39 @@ __device__ __forceinline__ int xcd_logical_block(int bid, int nblk) {
   return (xcd < rem) ? xcd * (per + 1) + kx : rem * (per + 1) + (xcd - rem) * per + kx;
 }
 
+// Where a lane's fp32 partials of a 32-row block lie in the workspace: float
+// offset of its first four (d block nb = 0, slots 0-3), and floats from four
+// to four (slot group q4, then d block: NB * 4 groups).  The block's 32 D
+// floats start at row r0.  Whole blocks are kept in accumulator order, so that
+// 64 lanes write (and the merge reads) 1 KB runs; in row order a store
+// instruction touches 32 rows.  A segment's last, shorter block is in row
+// order: the workspace holds exactly the rows there are.
+template <int D>
+__device__ __forceinline__ int64_t part_offset(int64_t r0, bool frag_order, int nb, int lane) {
+  return frag_order ? r0 * D + nb * 1024 + lane * 4 : (r0 + (lane & 31)) * D + nb * 32 + 4 * (lane >> 5);
+}
+__device__ __forceinline__ int part_step(bool frag_order) { return frag_order ? 256 : 8; }
+
+// 32 output columns of one row per lane pair: v[r] is column
+// 8 (r / 4) + 4 hh + r % 4.  The halves trade values (slots 8 t + 4 .. +7 of
+// the low half against slots 8 t .. +3 of the high half), so that a lane owns
+// eight consecutive columns and stores 16 bytes.  Every lane calls it; `ok`
+// lanes store.
+__device__ __forceinline__ void store_row32(const float (&v)[16], uint16_t* op, int hh, bool ok) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    bf16x8 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const auto x =
+          __builtin_amdgcn_permlane32_swap(__float_as_uint(v[8 * t + j]), __float_as_uint(v[8 * t + 4 + j]), false, false);
+      o[j] = (__bf16)__uint_as_float(x[0]);
+      o[4 + j] = (__bf16)__uint_as_float(x[1]);
+    }
+    if (ok) *reinterpret_cast<bf16x8*>(op + 16 * t + 8 * hh) = o;
+  }
+}
+
 // The query tile of rows seg_row0 .. of segment qs, batch b, head h, over the
 // segment's key tiles [kt_begin, kt_end).  part_row < 0: final output (bf16 O
 // and LSE); otherwise unnormalised fp32 partials (O, running max in log2
@@ -1237,39 +1270,36 @@ __device__ __forceinline__ void attend_tile(const Params& p, const QSeg& qs, int
   for (int qb = 0; qb < QB; ++qb) l_tot[qb] = sum_halves(lsum[qb]);
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    const int er = wave * RW + 32 * qb + (el & 31);  // row inside the tile
-    if (er >= e_valid) continue;
+    const int blk = wave * RW + 32 * qb, er = blk + (el & 31);  // block and row inside the tile
+    if (blk >= e_valid) continue;
     if (part_row >= 0) {
-      const int64_t prow = part_row + er;
-      float* op = p.ws_o + prow * D;
+      // kPingPong: partials of a whole 32-row block in accumulator order (see part_offset)
+      const bool frag_order = kPingPong && e_valid - blk >= 32;
+      if (er < e_valid) {
+        float* op = p.ws_o + part_offset<D>(part_row + blk, frag_order, 0, el);
+        const int step = part_step(frag_order);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = nb * 32 + 8 * q4 + 4 * ehh;
-          float4 v4 = make_float4(oacc[qb][nb][4 * q4], oacc[qb][nb][4 * q4 + 1], oacc[qb][nb][4 * q4 + 2],
-                                  oacc[qb][nb][4 * q4 + 3]);
-          *reinterpret_cast<float4*>(op + d) = v4;
-        }
-      if (ehh == 0) {
-        p.ws_ml[prow * 2] = m_used[qb];
-        p.ws_ml[prow * 2 + 1] = l_tot[qb];
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<float4*>(op + (nb * 4 + q4) * step) =
+                make_float4(oacc[qb][nb][4 * q4], oacc[qb][nb][4 * q4 + 1], oacc[qb][nb][4 * q4 + 2],
+                            oacc[qb][nb][4 * q4 + 3]);
+        if (ehh == 0)
+          *reinterpret_cast<float2*>(p.ws_ml + (part_row + er) * 2) = make_float2(m_used[qb], l_tot[qb]);
       }
     } else {
       const int grow = qs.row0 + seg_row0 + er;
       const float inv = l_tot[qb] > 0.f ? 1.f / l_tot[qb] : 0.f;
       uint16_t* op = p.o + int64_t(b) * p.o_sb + int64_t(grow) * p.o_st + int64_t(h) * D;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+      for (int nb = 0; nb < NB; ++nb) {
+        float v[16];
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const int d = nb * 32 + 8 * q4 + 4 * ehh;
-          __bf16 o4[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) o4[j] = (__bf16)(oacc[qb][nb][4 * q4 + j] * inv);
-          *reinterpret_cast<u32x2*>(op + d) = __builtin_bit_cast(u32x2, o4);
-        }
-      if (p.lse && ehh == 0)
+        for (int j = 0; j < 16; ++j) v[j] = oacc[qb][nb][j] * inv;
+        store_row32(v, op + nb * 32, ehh, er < e_valid);
+      }
+      if (p.lse && ehh == 0 && er < e_valid)
         p.lse[(int64_t(b) * p.H + h) * p.n_rows + grow] =
             l_tot[qb] > 0.f ? m_used[qb] * 0.69314718055994531f + __logf(l_tot[qb]) : -INFINITY;
     }
@@ -1521,77 +1551,122 @@ __global__ __launch_bounds__(256) void combine_balanced_kernel(const Params p, i
 }
 
 
-// Split-KV merge: O = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s, in split order.
-// One thread per (row, 4 consecutive d).
-// Merge of one output row's split partials, in split order: partial s of the
-// row sits at workspace row r0 + s * stride (D floats of O, then max and sum
-// in the (max, sum) plane).  Writes 4 bf16 of O (columns 4 d4..) and, for
-// d4 = 0, the LSE when lse is not null.
-__device__ __forceinline__ void merge_partials(const float* ws_o, const float* ws_ml, int64_t r0, int64_t stride,
-                                               int splits, int D, int d4, uint16_t* op, float* lse) {
+// Split-KV merge: O = sum_s 2^(m_s - M) acc_s / sum_s 2^(m_s - M) l_s, in split
+// order.  One wave merges 32 columns (d block nb) of a block of up to 32 rows:
+// partial s of the block sits at workspace row r0 + s * stride (O as
+// part_offset lays it out, then max and sum in the (max, sum) plane).
+//
+// HBM- and latency-bound: the partials of the first four splits are requested
+// before anything is waited for (16 loads of 16 bytes per lane), those of the
+// next four together again.  With one split at a time behind the test of its
+// sum, 57 MB of partials (three splits of a 512-pixel step) took 16.4 us.
+template <int D>
+__device__ __forceinline__ void merge_block(const float* ws_o, const float* ws_ml, int64_t r0, int64_t stride,
+                                            int splits, int valid, int nb, int lane, uint16_t* op, int64_t o_st,
+                                            float* lse) {
+  constexpr int CH = 4;
+  const bool frag_order = valid >= 32;
+  const int row = lane & 31, hh = lane >> 5;
+  const bool ok = row < valid;
+  const int la = ok ? lane : lane & 32;  // lanes past the block read its first row
+  const float* po = ws_o + part_offset<D>(r0, frag_order, nb, la);
+  const float* pml = ws_ml + (r0 + (la & 31)) * 2;
+  const int step = part_step(frag_order);
+  float4 o[CH][4];
+  float2 ml[CH];
+  const auto load = [&](int s0) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+      if (s0 + c < splits) {
+        ml[c] = *reinterpret_cast<const float2*>(pml + (s0 + c) * stride * 2);
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          o[c][q4] = *reinterpret_cast<const float4*>(po + (s0 + c) * stride * D + q4 * step);
+      }
+  };
+  load(0);
   float M = -INFINITY;
-  for (int s = 0; s < splits; ++s) {
-    const float ls = ws_ml[(s * stride + r0) * 2 + 1];
-    if (ls > 0.f) M = fmaxf(M, ws_ml[(s * stride + r0) * 2]);
+  for (int s0 = 0; s0 < splits; s0 += 8) {
+    float2 t[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (s0 + c < splits) t[c] = *reinterpret_cast<const float2*>(pml + (s0 + c) * stride * 2);
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (s0 + c < splits && t[c].y > 0.f) M = fmaxf(M, t[c].x);
   }
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  float acc[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) acc[j] = 0.f;
   float l = 0.f;
-  if (M != -INFINITY) {
-    for (int s = 0; s < splits; ++s) {
-      const float ls = ws_ml[(s * stride + r0) * 2 + 1];
-      if (!(ls > 0.f)) continue;
-      const float wgt = __builtin_amdgcn_exp2f(ws_ml[(s * stride + r0) * 2] - M);
-      const float4 o = *reinterpret_cast<const float4*>(ws_o + (s * stride + r0) * D + 4 * d4);
-      acc.x += wgt * o.x;
-      acc.y += wgt * o.y;
-      acc.z += wgt * o.z;
-      acc.w += wgt * o.w;
-      l += wgt * ls;
+  for (int s0 = 0; s0 < splits; s0 += CH) {
+    if (s0 > 0) load(s0);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      if (s0 + c >= splits || M == -INFINITY || !(ml[c].y > 0.f)) continue;
+      const float wgt = __builtin_amdgcn_exp2f(ml[c].x - M);
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        acc[4 * q4] += wgt * o[c][q4].x;
+        acc[4 * q4 + 1] += wgt * o[c][q4].y;
+        acc[4 * q4 + 2] += wgt * o[c][q4].z;
+        acc[4 * q4 + 3] += wgt * o[c][q4].w;
+      }
+      l += wgt * ml[c].y;
     }
   }
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  __bf16 o4[4] = {(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv), (__bf16)(acc.w * inv)};
-  *reinterpret_cast<u32x2*>(op) = __builtin_bit_cast(u32x2, o4);
-  if (lse && d4 == 0) *lse = l > 0.f ? M * 0.69314718055994531f + __logf(l) : -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) acc[j] *= inv;
+  store_row32(acc, op + row * o_st + nb * 32, hh, ok);
+  if (lse && nb == 0 && hh == 0 && ok) lse[row] = l > 0.f ? M * 0.69314718055994531f + __logf(l) : -INFINITY;
 }
 
+// Even and tail splits: one wave per (batch, head, 32-row block, d block).
+template <int D>
 __global__ __launch_bounds__(256) void combine_kernel(const CombineParams c) {
-  const int dq = c.D / 4;
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t total = int64_t(c.B) * c.H * c.n_rows * dq;
-  if (idx >= total) return;
-  const int d4 = int(idx % dq);
-  const int64_t bhr = idx / dq;  // (b*H + h)*n_rows + row
-  const int row = int(bhr % c.n_rows);
-  const int64_t bh = bhr / c.n_rows;
+  constexpr int NB = D / 32;
+  const int lane = threadIdx.x & 63;
+  int64_t w = int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = int(w % NB);
+  w /= NB;
+  const int64_t bh = w / c.n_blocks;
+  const int blk = int(w % c.n_blocks);
+  if (bh >= int64_t(c.B) * c.H) return;
+  int i = 0;
+  while (i + 1 < c.n_seg && c.seg[i + 1].block0 <= blk) ++i;
+  const int in_seg = (blk - c.seg[i].block0) * 32, row = c.seg[i].row0 + in_seg;
   const int h = int(bh % c.H), b = int(bh / c.H);
-  const int64_t plane = int64_t(c.B) * c.H * c.n_rows;
-  uint16_t* op = c.o + int64_t(b) * c.o_sb + int64_t(row) * c.o_st + int64_t(h) * c.D + 4 * d4;
-  merge_partials(c.ws_o, c.ws_ml, bhr, plane, c.splits, c.D, d4, op, c.lse ? c.lse + bhr : nullptr);
+  merge_block<D>(c.ws_o, c.ws_ml, bh * c.n_rows + row, int64_t(c.B) * c.H * c.n_rows, c.splits,
+                 c.seg[i].len - in_seg, nb, lane,
+                 c.o + int64_t(b) * c.o_sb + int64_t(row) * c.o_st + int64_t(h) * D, c.o_st,
+                 c.lse ? c.lse + bh * c.n_rows + row : nullptr);
 }
 
-// Merge of the last-round split: one thread per 4 output elements of the
-// p.lr_tiles last query tiles (logical order); piece s of tile i holds row r
-// at workspace row (s T + i) BM + r.
-__global__ __launch_bounds__(256) void combine_last_round_kernel(const Params p, int D) {
-  const int dq = D / 4;
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// Last-round split: one wave per (tile of the p.lr_tiles last query tiles in
+// logical order, 32-row block, d block); piece s of tile i holds row r at
+// workspace row (s T + i) BM + r.
+template <int D>
+__global__ __launch_bounds__(256) void combine_last_round_kernel(const Params p) {
+  constexpr int NB = D / 32, BM = rows_per_wg(kQBPlain);
+  const int lane = threadIdx.x & 63;
+  int64_t w = int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int T = p.lr_tiles;
-  if (idx >= int64_t(T) * p.bm * dq) return;
-  const int d4 = int(idx % dq);
-  const int64_t ir = idx / dq;
-  const int r = int(ir % p.bm), i = int(ir / p.bm);
-  const int64_t w = int64_t(p.B) * p.H * p.n_qtiles - T + i;
-  const int t = int(w % p.n_qtiles);
-  const int64_t bh = w / p.n_qtiles;
+  const int nb = int(w % NB);
+  w /= NB;
+  const int blk = int(w % (BM / 32)), i = int(w / (BM / 32));
+  if (i >= T) return;
+  const int64_t tw = int64_t(p.B) * p.H * p.n_qtiles - T + i;
+  const int t = int(tw % p.n_qtiles);
+  const int64_t bh = tw / p.n_qtiles;
   const int h = int(bh % p.H), b = int(bh / p.H);
   int qi = 0;
   while (qi + 1 < p.n_qseg && p.qseg[qi + 1].tile0 <= t) ++qi;
-  const int in_seg = (t - p.qseg[qi].tile0) * p.bm + r;
+  const int in_seg = (t - p.qseg[qi].tile0) * BM + blk * 32;
   if (in_seg >= p.qseg[qi].len) return;
   const int row = p.qseg[qi].row0 + in_seg;
-  uint16_t* op = p.o + int64_t(b) * p.o_sb + int64_t(row) * p.o_st + int64_t(h) * D + 4 * d4;
-  merge_partials(p.ws_o, p.ws_ml, int64_t(i) * p.bm + r, int64_t(T) * p.bm, 2, D, d4, op,
+  merge_block<D>(p.ws_o, p.ws_ml, int64_t(i) * BM + blk * 32, int64_t(T) * BM, 2, p.qseg[qi].len - in_seg, nb, lane,
+                 p.o + int64_t(b) * p.o_sb + int64_t(row) * p.o_st + int64_t(h) * D, p.o_st,
                  p.lse ? p.lse + bh * p.n_rows + row : nullptr);
 }
 
@@ -1721,17 +1796,23 @@ int launch_combine_balanced(const Params& p, int D, void* stream) {
 }
 
 int launch_combine_last_round(const Params& p, int D, void* stream) {
-  const int64_t total = int64_t(p.lr_tiles) * p.bm * (D / 4);
-  if (total == 0) return 0;
-  hipLaunchKernelGGL(combine_last_round_kernel, dim3((total + 255) / 256), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), p, D);
+  // four waves a work-group, each 32 rows x 32 columns
+  const int64_t waves = int64_t(p.lr_tiles) * (p.bm / 32) * (D / 32);
+  if (waves == 0) return 0;
+  const dim3 g((waves + 3) / 4), t(256);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (D == 128) hipLaunchKernelGGL((combine_last_round_kernel<128>), g, t, 0, s, p);
+  else hipLaunchKernelGGL((combine_last_round_kernel<64>), g, t, 0, s, p);
   return int(hipGetLastError());
 }
 
 int launch_combine(const CombineParams& c, void* stream) {
-  const int64_t total = int64_t(c.B) * c.H * c.n_rows * (c.D / 4);
-  if (total == 0) return 0;
-  hipLaunchKernelGGL(combine_kernel, dim3((total + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(stream), c);
+  const int64_t waves = int64_t(c.B) * c.H * c.n_blocks * (c.D / 32);
+  if (waves == 0) return 0;
+  const dim3 g((waves + 3) / 4), t(256);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (c.D == 128) hipLaunchKernelGGL((combine_kernel<128>), g, t, 0, s, c);
+  else hipLaunchKernelGGL((combine_kernel<64>), g, t, 0, s, c);
   return int(hipGetLastError());
 }
 

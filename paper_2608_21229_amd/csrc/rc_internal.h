@@ -91,7 +91,7 @@ struct Params {
   uint16_t* o;
   int64_t o_sb, o_st;
   float* lse;          // [B, H, n_rows] or null
-  float* ws_o;         // split partials [splits, B, H, n_rows, D] (unnormalised)
+  float* ws_o;         // split partials [splits, B, H, n_rows, D] (unnormalised; 32-row blocks in accumulator order)
   float* ws_ml;        // split partials [splits, B, H, n_rows, 2] (max in log2 units, sum)
   KeySrc src[2];
   int32_t B, H, n_rows, n_qseg, n_qtiles, splits;  // splits: kSplitsBalanced = balanced schedule
@@ -160,6 +160,10 @@ struct CombineParams {
   float* lse;
   int64_t o_sb, o_st;
   int32_t B, H, D, n_rows, splits;
+  int32_t n_seg, n_blocks;  // query segments and their 32-row blocks, per (batch, head)
+  struct Seg {
+    int32_t row0, len, block0;  // first row, rows, first block
+  } seg[RC_MAX_SEGMENTS];
 };
 
 // Host-side planning (layout.cpp).

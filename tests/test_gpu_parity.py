@@ -546,3 +546,34 @@ def test_half_tiles_match_whole_tiles(lens, D, fp8):
         O, _, _ = oa.denoise_step(inp.kinds, inp.lens, om.perref_mask(inp.kinds), *(f64(t) for t in inp.live), f64(k),
                                   f64(v), wl.scale, rows=rows)
         check(whole[1], O, f"half tiles {lens} D={D}", rows)
+
+
+@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("lens,splits", [((33, 31), 2), ((1, 64), 5), ((32, 95), 9), ((16, 520), 32),
+                                         ((300, 700), rc.SPLITS_TAIL)])
+def test_split_merge_row_blocks(lens, splits, D, fp8):
+    """The merge of split partials: whole 32-row blocks and shorter last ones,
+    one to eight rounds of four splits, splits without keys, every row and the
+    LSE against the oracle (over the FP8 cache: against the unsplit step,
+    whose differences are the order of fp32 sums and one bf16 rounding)."""
+    from synthgen import Workload
+    lt, x = lens
+    wl = Workload("merge", 2, 2, D, ((0, 8), (1, lt), (2, x), (3, 500)), std=1.0, seed=37)
+    print(f"[case] split merge lens={lens} splits={splits} D={D} fp8={fp8}", flush=True)
+    inp = draw_inputs(wl)
+    L = layout_for(inp, "perref")
+    if fp8:
+        _, _, k8, v8, sc = rc.ref_kv_prefill_fp8(L, *(t.to(DEV) for t in inp.static), scale=wl.scale)
+        lv = [t.to(DEV) for t in inp.live]
+        o, lse = rc.step_masked_attention_fp8(L, *lv, k8, v8, sc, splits=splits, scale=wl.scale, want_lse=True)
+        o1, lse1 = rc.step_masked_attention_fp8(L, *lv, k8, v8, sc, splits=1, scale=wl.scale, want_lse=True)
+        torch.cuda.synchronize()
+        check(o, f64(o1), f"split merge {lens} {splits} fp8")
+        check_lse(lse, f64(lse1), f"split merge {lens} {splits} fp8")
+        return
+    _, _, kc, vc = run_prefill(L, inp, wl.scale, want_lse=False)
+    o, lse = run_step(L, inp, kc, vc, wl.scale, splits=splits)
+    torch.cuda.synchronize()
+    O, ls, _ = oracle_step(inp, oracle_mask(inp, "perref"), f64(kc), f64(vc), wl.scale)
+    check(o, O, f"split merge {lens} {splits}")
+    check_lse(lse, ls, f"split merge {lens} {splits}")
