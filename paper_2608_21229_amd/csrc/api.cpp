@@ -244,6 +244,32 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   for (int i = 0; i < n_copy; ++i) c.seg[i] = seg[i];
   // the quantising store's grids: (B H) x row blocks (amax), one thread per
   // 16-byte granule of K and of V
+  if (n_cached > 0) {
+    // amax work-groups at the end of the attention grid take the (batch,
+    // head)s that fit on the CUs its partial last round leaves free
+    const CopyPlan cpl = plan_copy_tail(p, n_cached);
+    c.bh0 = cpl.blocks > 0 ? int32_t(cpl.rows / n_cached) : 0;
+    CopyTail& t = p.cp;
+    t.B = B;
+    t.H = H;
+    if (c.bh0 > 0) {
+      t.k_src = c.k_src;
+      t.v_src = c.v_src;
+      t.k_dst = reinterpret_cast<uint16_t*>(c.k_dst);  // not written: the quantising store follows
+      t.v_dst = reinterpret_cast<uint16_t*>(c.v_dst);
+      t.src_sb = c.src_sb;
+      t.src_st = c.src_st;
+      t.n_cached = c.n_cached;
+      t.n_copy = c.n_copy;
+      for (int i = 0; i < n_copy; ++i) t.seg[i] = seg[i];
+      t.blocks = cpl.blocks;
+      t.rows = c.bh0 * c.n_cached;
+      t.amax = kv_scale;
+      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + cpl.blocks, "prefill attention"));
+    } else {
+      p.amax_clear = kv_scale;
+    }
+  }
   p.half_tiles = half_tiles(p);
   RC_TRY(check_blocks(int64_t(B) * H, "FP8 cache store"));
   RC_TRY(check_blocks((int64_t(B) * H * n_cached * (D / 8) + 255) / 256, "FP8 cache store"));

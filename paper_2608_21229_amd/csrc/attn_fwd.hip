@@ -46,6 +46,7 @@
 
 #include <mutex>
 
+#include "rc_device.h"
 #include "rc_internal.h"
 
 namespace rc {
@@ -54,8 +55,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
@@ -1354,8 +1353,63 @@ __device__ __forceinline__ void copy_tail(const CopyTail& c, int j, int tid) {
   }
 }
 
+// Amax work-group j of the FP8 prefill: the largest |K| and |V| of its share of
+// the first c.rows flat cache rows (whole (batch, head)s), as copy_tail reads
+// them; per (batch, head) one maximum a wave, merged by an atomic max (whose
+// result does not depend on the order).
+template <int D>
+__device__ __forceinline__ void amax_tail(const CopyTail& c, int j, int tid) {
+  constexpr int GR = D / 8, RPP = kThreads / GR, U = 8;
+  const uint32_t H = uint32_t(c.H), n = uint32_t(c.n_cached), R = uint32_t(c.rows);
+  const uint32_t r1 = uint32_t(uint64_t(R) * uint32_t(j + 1) / uint32_t(c.blocks));
+  const int g8 = (tid % GR) * 8;
+  for (uint32_t r0 = uint32_t(uint64_t(R) * uint32_t(j) / uint32_t(c.blocks)); r0 < r1;) {
+    const uint32_t bh = r0 / n, b = bh / H, h = bh - b * H;
+    const uint32_t e = min(r1, (bh + 1) * n);
+    float mk = 0.f, mv = 0.f;
+    for (uint32_t base = r0 + uint32_t(tid / GR); base < e; base += uint32_t(RPP * U)) {
+      u32x4 kx[U], vx[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t r = base + uint32_t(u * RPP);
+        kx[u] = vx[u] = u32x4{0u, 0u, 0u, 0u};
+        if (r < e) {
+          const uint32_t drow = r - bh * n;
+          int64_t delta = 0;  // uniform loop over the run table (see copy_tail)
+          for (int k = 0; k < c.n_copy; ++k)
+            if (drow >= uint32_t(c.seg[k].dst_row0)) delta = int64_t(c.seg[k].src_row0) - c.seg[k].dst_row0;
+          const int64_t so = int64_t(b) * c.src_sb + (int64_t(drow) + delta) * c.src_st + int64_t(h) * D + g8;
+          kx[u] = *reinterpret_cast<const u32x4*>(c.k_src + so);
+          vx[u] = *reinterpret_cast<const u32x4*>(c.v_src + so);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        mk = fmaxf(mk, amax8(kx[u]));
+        mv = fmaxf(mv, amax8(vx[u]));
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      mk = fmaxf(mk, __shfl_xor(mk, o));
+      mv = fmaxf(mv, __shfl_xor(mv, o));
+    }
+    if ((tid & 63) == 0) {  // non-negative floats order like their bit patterns
+      atomicMax(reinterpret_cast<unsigned int*>(c.amax + bh * 2), __float_as_uint(mk));
+      atomicMax(reinterpret_cast<unsigned int*>(c.amax + bh * 2 + 1), __float_as_uint(mv));
+    }
+    r0 = e;
+  }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(float* a, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) a[i] = 0.f;
+}
+
 // One work-group per (batch, head, query tile, key split), then p.cp.blocks
-// copy work-groups (the prefill's cache store; unsplit bf16 launches only).
+// copy work-groups (the prefill's cache store, or its amax for the FP8 cache;
+// unsplit launches over bf16 keys only).
 // The host plans query tiles of p.bm = rows_per_wg(kQBPlain) = 512 rows.
 //
 // A tile, or what is left of one, of at most 256 rows runs with one 32-row
@@ -1373,9 +1427,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
   if constexpr (!kSplit && !kF8) {
     n_attn -= p.cp.blocks;
     if (int(blockIdx.x) >= n_attn) {
-      copy_tail<D>(p.cp, blockIdx.x - n_attn, tid);
+      if (p.cp.amax) amax_tail<D>(p.cp, blockIdx.x - n_attn, tid);
+      else copy_tail<D>(p.cp, blockIdx.x - n_attn, tid);
       return;
     }
+    // the accumulators of the amax launch that follows (with amax work-groups
+    // in this grid, a launch before has cleared them)
+    if (p.amax_clear && blockIdx.x == 0)
+      for (int64_t i = tid; i < int64_t(p.cp.B) * p.cp.H * 2; i += kThreads) p.amax_clear[i] = 0.f;
   }
   int split, rest, half = -1;  // half: which 256 rows of the tile, -1 for all
   int lr_tile = 0;             // last-round split: index among its tiles
@@ -1745,6 +1804,10 @@ int launch_attention(const Params& p, int D, void* stream) {
   // no copy path)
   if (p.cp.blocks < 0 || (p.cp.blocks > 0 && (p.splits != 1 || p.fp8))) return int(hipErrorInvalidValue);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (p.cp.blocks > 0 && p.cp.amax) {
+    const int n = p.cp.B * p.cp.H * 2;
+    hipLaunchKernelGGL(clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p.cp.amax, n);
+  }
   const auto launch = [&](const Params& q, int64_t nb) {
     nb += q.cp.blocks;
     if (D == 128) q.fp8 ? launch_grid<128, true>(q, nb, s) : launch_grid<128, false>(q, nb, s);

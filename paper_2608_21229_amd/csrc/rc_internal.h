@@ -72,6 +72,8 @@ struct CopyTail {
   int32_t B, H, n_cached, n_copy;
   int32_t blocks;          // copy work-groups at the end of the grid (0: none)
   int32_t rows;            // flat cache rows (b, h, row) [0, rows) that they copy
+  float* amax;             // FP8 cache: instead of copying, take the rows' largest magnitudes per (batch, head)
+                           // into [B, H, 2] (K, V), which a launch before has cleared
   CopySeg seg[RC_MAX_SEGMENTS];
 };
 
@@ -110,6 +112,7 @@ struct Params {
   QSeg qseg[RC_MAX_SEGMENTS];
   KeyRange range[kMaxRanges];
   CopyTail cp;         // prefill only; cp.blocks = 0 elsewhere
+  float* amax_clear;   // FP8 prefill: [B, H, 2] amax accumulators to clear (null elsewhere)
 };
 
 // Cache store: copy rows of the cached segments from the static K/V buffers
@@ -139,6 +142,7 @@ struct CacheStore8Params {
   float* kv_scale;     // [B, H, 2]: amax while quantising, the scales afterwards
   int64_t src_sb, src_st;
   int32_t B, H, D, n_cached, n_copy;
+  int32_t bh0;         // the attention launch has taken the amax of the (batch, head)s before this one
   CopySeg seg[RC_MAX_SEGMENTS];
 };
 

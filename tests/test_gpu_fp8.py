@@ -142,3 +142,40 @@ def test_fp8_refuses_balanced_schedule():
     with pytest.raises(rc.RcError) as e:
         rc.step_masked_attention_fp8(L, ql, kl, vl, k8, v8, sc, splits=rc.SPLITS_BALANCED)
     assert e.value.status == rc.RC_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("lens,mask,B,H,D,part", [
+    ((64, [256, 256, 256]), "paper", 2, 32, 64, 0.0),                       # a whole round: no idle CU
+    ((64, [4096, 4096, 4096, 4096, 4096]), "perref", 1, 24, 128, 0.5),      # half of the heads fit
+    ((17, [700, 33]), "perref", 2, 3, 128, 1.0),                            # all of them
+    ((5, [100]), "paper", 1, 1, 64, 1.0),                                   # one work-group, rows off its stride
+])
+def test_fp8_amax_work_groups(lens, mask, B, H, D, part):
+    """The scales and codes whichever launch takes a head's largest magnitude:
+    the amax work-groups of the attention launch (as many whole heads as the
+    copy plan's rows hold) or the launch after it.  By definition: the smallest
+    power of two with amax / s <= 448, and torch's e4m3fn conversion of x / s.
+    K and V get their largest value in the first and the last cached row."""
+    st, refs = lens
+    L = rc.Layout([(0, st), (1, 64), (2, 256)] + [(3, n) for n in refs], mask)
+    nc = L.rows(rc.ROWS_CACHED)
+    _, wgs, rows = L.prefill_plan(B, H, D)
+    heads = rows // nc if wgs else 0
+    print(f"[case] fp8 amax lens={lens} {mask} B={B} H={H} D={D}: {heads} of {B * H} heads in the attention", flush=True)
+    assert (heads == 0) if part == 0.0 else (heads == B * H) if part == 1.0 else 0 < heads < B * H
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q, k, v = (torch.randn((B, L.rows(rc.ROWS_STATIC), H, D), generator=g, device="cuda").to(torch.bfloat16)
+               for _ in range(3))
+    first = st if mask == "paper" else 0
+    k[:, first, :, 0] = 9.0
+    v[:, -1, :, D - 1] = -11.0
+    _, _, k8, v8, sc = rc.ref_kv_prefill_fp8(L, q, k, v)
+    sc.fill_(1e9)  # whatever the buffer held before
+    rc.ref_kv_prefill_fp8(L, q, k, v, k_cache8=k8, v_cache8=v8, kv_scale=sc)
+    torch.cuda.synchronize()
+    for i, (x, x8) in enumerate(((k, k8), (v, v8))):
+        xc = x[:, first:].permute(0, 2, 1, 3).float()
+        s = torch.exp2(torch.ceil(torch.log2(xc.abs().amax(dim=(2, 3)) / 448.0)))
+        assert torch.equal(sc[:, :, i], s)
+        assert torch.equal(x8, (xc / s[:, :, None, None]).to(torch.float8_e4m3fn).view(torch.uint8))
