@@ -6,7 +6,8 @@
 // accumulation, one bf16 rounding (RNE) at the end.
 //
 // Output tiles of 256 x 256 down to 64 x 64 (one work-group each, chosen by
-// the number of rounds over the CUs); each wave owns a block of
+// the number of rounds over the CUs; a partial last round of 256 x 256 tiles
+// may run in smaller ones); each wave owns a block of
 // v_mfma_f32_32x32x16_bf16 accumulators.  K advances in slices of 64: the A
 // and W tiles (64 k per row, 128-byte rows) stream through an LDS ring with
 // direct global->LDS loads; 16-byte granule g of row r is stored at slot
@@ -16,6 +17,8 @@
 // neither on the other rows nor on the tile that holds it.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "rc_internal.h"
 
@@ -79,10 +82,9 @@ __device__ __forceinline__ int64_t lin_xcd_block(int64_t bid, int64_t nblk) {
 // a group, so that the work-groups an XCD runs together share A and W tiles.
 constexpr int kGroupM = 4;
 template <int BM, int BN>
-__device__ __forceinline__ void lin_tile(const LinearParams& q, int64_t& m0, int& n0) {
+__device__ __forceinline__ void lin_tile(const LinearParams& q, int64_t w, int64_t& m0, int& n0) {
   const int64_t n_tiles = q.N / BN;
   const int64_t m_tiles = (q.M + BM - 1) / BM;
-  const int64_t w = lin_xcd_block(blockIdx.x, gridDim.x);
   const int64_t per_group = int64_t(kGroupM) * n_tiles;
   const int64_t first_m = (w / per_group) * kGroupM;
   const int64_t group_m = min(int64_t(kGroupM), m_tiles - first_m);
@@ -139,7 +141,7 @@ __device__ __forceinline__ void lin_store_block(const LinearParams& q, f32x16 ac
 // before the barrier, 128 x 128 blocks on four waves (within noise), 128 x 256
 // tiles, 32-row tiles, two work-groups per CU for the small tiles.
 template <int MB, int NB, int WM, int WN, int KS, int ST, int SP>
-__global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams q) {
+__device__ __forceinline__ void linear_tile(const LinearParams& q, char* ring, int64_t m0, int n0) {
   constexpr int NW = WM * WN;
   constexpr int BM = 32 * MB * WM, BN = 32 * NB * WN;
   constexpr int CA = BM / 8 / NW, CW = BN / 8 / NW;  // 1 KB chunks per wave per slice
@@ -147,13 +149,9 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
   constexpr int kSlice = (BM + BN) * kLinBK * 2, kStage = KS * kSlice;
   constexpr int kLoads = KS * (CA + CW);
   static_assert(ST * kLoads <= 63, "vmcnt range");
-  __shared__ __attribute__((aligned(1024))) char ring[ST * kStage];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  int64_t m0;
-  int n0;
-  lin_tile<BM, BN>(q, m0, n0);
 
   uint32_t aoff[CA], woff[CW];
 #pragma unroll
@@ -252,6 +250,67 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
       lin_store_block(q, acc[i][j], m0 + wm * 32 * MB + i * 32 + (lane & 31), n0 + wn * 32 * NB + j * 32, lane >> 5);
 }
 
+template <int MB, int NB, int WM, int WN, int KS, int ST>
+constexpr int kRingBytes = ST * KS * 32 * (MB * WM + NB * WN) * kLinBK * 2;
+
+// A grid of one tile size.
+template <int MB, int NB, int WM, int WN, int KS, int ST, int SP>
+__global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams q) {
+  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes<MB, NB, WM, WN, KS, ST>];
+  int64_t m0;
+  int n0;
+  lin_tile<32 * MB * WM, 32 * NB * WN>(q, lin_xcd_block(blockIdx.x, gridDim.x), m0, n0);
+  linear_tile<MB, NB, WM, WN, KS, ST, SP>(q, ring, m0, n0);
+}
+
+// A grid of 256 x 256 tiles whose last partial round is cut into smaller parts,
+// so that the round ends sooner: tiles [end[l - 1], end[l]) (logical order) run
+// in parts of level l, each level's parts after the one before, on the CUs
+// that become free.  Same bits as whole tiles.  The chip is power-bound in
+// full rounds (about 79 us each at K = 3072 with all CUs busy), so cutting only
+// recovers what a round's idle CUs do not give back in clock: 1.125 rounds of
+// N = 9216, K = 3072 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 ->
+// 185, 2.53 rounds 221 -> 218, 4.2 rounds 361 -> 336; 1.1 rounds of N = K = 1024
+// 49 -> 40 us.  The two smallest levels run on four of the work-group's waves:
+// as fast as on eight.
+constexpr int kLevels = 4;
+constexpr int kLevelM[kLevels] = {256, 256, 128, 64}, kLevelN[kLevels] = {256, 128, 128, 128};
+constexpr int level_parts(int l) { return 65536 / (kLevelM[l] * kLevelN[l]); }
+struct LinCut {
+  int64_t end[kLevels];
+};
+
+__global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, const LinCut cut) {
+  __shared__ __attribute__((aligned(1024))) char ring[kRingBytes<2, 2, 4, 2, 1, 3>];
+  static_assert(sizeof(ring) >= size_t(kRingBytes<4, 2, 2, 4, 1, 2>), "ring");
+  static_assert(sizeof(ring) >= size_t(kRingBytes<2, 2, 2, 2, 1, 4>), "ring");
+  static_assert(sizeof(ring) >= size_t(kRingBytes<2, 1, 1, 4, 1, 6>), "ring");
+  int64_t i = blockIdx.x, first = 0;
+  int l = 0;
+  for (; l < kLevels - 1; ++l) {
+    const int64_t n = (cut.end[l] - first) * level_parts(l);
+    if (i < n) break;
+    i -= n;
+    first = cut.end[l];
+  }
+  const int parts = level_parts(l), across = 256 / kLevelN[l];
+  const int64_t w = lin_xcd_block(i, (cut.end[l] - first) * parts);
+  const int part = int(w % parts);
+  int64_t m0;
+  int n0;
+  lin_tile<256, 256>(q, first + w / parts, m0, n0);
+  m0 += part / across * kLevelM[l];
+  n0 += part % across * kLevelN[l];
+  if (m0 >= q.M) return;
+  if (l >= 2 && threadIdx.x >= 256) return;  // barriers wait for the waves that remain
+  switch (l) {
+    case 0: linear_tile<4, 2, 2, 4, 1, 2, 3>(q, ring, m0, n0); break;
+    case 1: linear_tile<2, 2, 4, 2, 1, 3, 8>(q, ring, m0, n0); break;
+    case 2: linear_tile<2, 2, 2, 2, 1, 4, 8>(q, ring, m0, n0); break;
+    default: linear_tile<2, 1, 1, 4, 1, 6, 3>(q, ring, m0, n0); break;
+  }
+}
+
 template <int MB, int NB, int WM, int WN, int KS, int ST, int SP>
 void launch_tile(const LinearParams& q, hipStream_t s) {
   constexpr int BM = 32 * MB * WM, BN = 32 * NB * WN;
@@ -272,9 +331,8 @@ struct LinTile {
 };
 constexpr LinTile kLinTiles[] = {{256, 256, 71}, {256, 128, 41}, {128, 128, 25}, {64, 128, 18}, {64, 64, 12}};
 
-int pick_linear(const LinearParams& q) {
+int pick_linear(const LinearParams& q, int64_t& best_cost) {
   int best = -1;
-  int64_t best_cost = 0;
   for (int i = 0; i < 5; ++i) {
     const LinTile t = kLinTiles[i];
     if (q.N % t.bn != 0) continue;
@@ -288,12 +346,49 @@ int pick_linear(const LinearParams& q) {
   return best;
 }
 
+// The cheapest cut of `tiles` 256 x 256 tiles from tile `first` on: a level
+// takes its whole rounds and leaves the rest to the next, or takes everything.
+// Costs in the units of kLinTiles, of rounds next to those of other levels: the
+// parts start when CUs become free, not all at once.  The last level costs less
+// where it fills less than half of the CUs (three levels for 136 tiles over
+// whole rounds gain 1.5%; for 160, with the last round full, they lose 1%).
+constexpr int64_t kLevelCost[kLevels] = {71, 45, 30, 27};
+constexpr int64_t kLastHalfCost = 18;
+
+int64_t plan_cut(int64_t tiles, int l, int64_t first, LinCut& cut) {
+  const int64_t blocks = (tiles - first) * level_parts(l);
+  LinCut all = cut;
+  for (int i = l; i < kLevels; ++i) all.end[i] = tiles;
+  const int64_t all_cost = l == kLevels - 1 && 2 * blocks <= kCUs ? (blocks > 0 ? kLastHalfCost : 0)
+                                                                  : (blocks + kCUs - 1) / kCUs * kLevelCost[l];
+  if (l == kLevels - 1 || blocks % kCUs == 0) {
+    cut = all;
+    return all_cost;
+  }
+  const int64_t rounds = blocks / kCUs;
+  LinCut sub = cut;
+  sub.end[l] = first + rounds * kCUs / level_parts(l);
+  const int64_t sub_cost = rounds * kLevelCost[l] + plan_cut(tiles, l + 1, sub.end[l], sub);
+  cut = sub_cost < all_cost ? sub : all;
+  return std::min(sub_cost, all_cost);
+}
+
 }  // namespace
 
 int launch_linear(const LinearParams& q, void* stream) {
   if (q.M == 0) return 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  switch (pick_linear(q)) {
+  int64_t cost = 0;
+  const int tile = pick_linear(q, cost);
+  const int64_t tiles = q.N % 256 == 0 ? (q.M + 255) / 256 * (q.N / 256) : 0;
+  LinCut cut{};
+  if (tiles > kCUs && plan_cut(tiles, 0, 0, cut) < cost) {
+    int64_t blocks = 0;
+    for (int l = 0; l < kLevels; ++l) blocks += (cut.end[l] - (l ? cut.end[l - 1] : 0)) * level_parts(l);
+    hipLaunchKernelGGL(linear_cut_kernel, dim3(blocks), dim3(512), 0, s, q, cut);
+    return int(hipGetLastError());
+  }
+  switch (tile) {
     case 0: launch_tile<4, 2, 2, 4, 1, 2, 3>(q, s); break;
     case 1: launch_tile<2, 2, 4, 2, 1, 3, 8>(q, s); break;
     case 2: launch_tile<2, 2, 2, 2, 1, 4, 8>(q, s); break;

@@ -174,6 +174,30 @@ def test_linear_every_tile(M, N, K, resid):
         assert torch.equal(alone, got[i:i + 1]), i
 
 
+# More than one round of 256 x 256 tiles: the last partial one in 64 x 128,
+# 128 x 128 or 256 x 128 parts, in 256 x 128 and 64 x 128 ones, or whole; the
+# last 64-row parts lie past M.  Every row against the same rows in calls of
+# their own (at most 64 tiles, one size), sampled rows against the oracle.
+@pytest.mark.parametrize("m_tiles,K,resid", [(33, 64, True), (36, 192, False), (40, 64, True), (44, 64, False),
+                                             (48, 128, False), (49, 64, True), (53, 64, False), (71, 64, False)])
+def test_linear_cut_last_round(m_tiles, K, resid):
+    M, N = 256 * m_tiles - 100, 2048
+    a, w = _bf((M, K), 51 + M), _bf((N, K), 52, K ** -0.5)
+    r = _bf((M, N), 53) if resid else None
+    a_d, w_d, r_d = a.to(DEV), w.to(DEV), None if r is None else r.to(DEV)
+    out = torch.full((M, N + 128), 7.0, dtype=torch.bfloat16, device=DEV)
+    got = rc.linear(a_d, w_d, residual=r_d, out=out[:, :N])
+    parts = torch.cat([rc.linear(a_d[i:i + 2048], w_d, residual=None if r is None else r_d[i:i + 2048])
+                       for i in range(0, M, 2048)])
+    torch.cuda.synchronize()
+    assert torch.equal(got, parts)
+    assert bool((out[:, N:] == 7.0).all()), "wrote outside the output view"
+    rows = np.sort(np.random.default_rng(M).choice(M, 64, replace=False))
+    want = oc.project(f64(a[rows]), f64(w), None if r is None else f64(r[rows]))
+    check_projection(got[rows], want, f"linear cut M={M} K={K} resid={resid}", f64(a[rows]), f64(w),
+                     None if r is None else f64(r[rows]))
+
+
 # ------------------------------------------------------------- chained layers
 def _wl(name, B, H, D, lens_st_lt_x, refs, seed=42):
     st, lt, x = lens_st_lt_x
