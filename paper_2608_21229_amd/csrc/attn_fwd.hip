@@ -1464,7 +1464,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
     split = blockIdx.x >= q;
     rest = xcd_logical_block(blockIdx.x - split * q, q);
   } else if (kSplit) {
-    const int w = xcd_logical_block(blockIdx.x, n_attn);
+    int w = xcd_logical_block(blockIdx.x, n_attn);
+    if (p.half_tiles > 0) {
+      half = w & 1;
+      w >>= 1;
+    }
     split = w % p.splits;
     rest = w / p.splits;
   } else {
@@ -1791,14 +1795,17 @@ int launch_attention(const Params& p, int D, void* stream) {
   // the last-round split adds one short piece per split tile; a tile (or
   // piece) run as two halves adds one work-group
   const int64_t blocks = p.lr_tiles > 0 ? tiles + p.lr_tiles + (p.half_tiles > 0 ? 2 * int64_t(p.lr_tiles) : 0)
-                                        : tiles * p.splits + p.half_tiles;
+                                        : (tiles + p.half_tiles) * p.splits;
   if (blocks == 0) return 0;
   if (p.lr_tiles < 0 || (p.lr_tiles > 0 && (p.splits != 2 || p.tail_num <= 0 || p.lr_tiles > tiles)))
     return int(hipErrorInvalidValue);
-  // halves are the last tiles of an unsplit grid or all tiles of a last-round
-  // split
+  // halves are the last tiles of an unsplit grid, all tiles of an even split
+  // or all those of a last-round split
   if (p.half_tiles < 0 || p.half_tiles > tiles ||
-      (p.half_tiles > 0 && (p.lr_tiles > 0 ? p.half_tiles != p.lr_tiles : p.splits != 1 || per_batch_launches(p))))
+      (p.half_tiles > 0 && (p.lr_tiles > 0     ? p.half_tiles != p.lr_tiles
+                            : p.tail_num > 0   ? true
+                            : p.splits > 1     ? p.half_tiles != tiles
+                                               : per_batch_launches(p))))
     return int(hipErrorInvalidValue);
   // copy work-groups ride on unsplit bf16 grids only (the other kernels have
   // no copy path)

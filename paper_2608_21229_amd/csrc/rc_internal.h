@@ -102,7 +102,8 @@ struct Params {
   int32_t lr_tiles;    // last-round split (splits = 2, tail_num > 0): only the last lr_tiles query tiles
                        // (logical order) run as a long and a short piece; the others whole, written directly
   int32_t half_tiles;  // unsplit grid: the last half_tiles query tiles (logical order) run as two work-groups of
-                       // half the rows; last-round split: lr_tiles when its pieces do, else 0
+                       // half the rows; even split: all tiles when they do (else 0); last-round split: lr_tiles
+                       // when its pieces do, else 0
   int32_t fp8;         // key source 1 is the FP8 cache
   const float* kv_scale;  // FP8 cache: [B, H, 2] power-of-two scales of K and V
   int64_t units_bh;    // key-tile units (query tile x key tile) per (batch, head)

@@ -549,6 +549,43 @@ def test_half_tiles_match_whole_tiles(lens, D, fp8):
 
 
 @pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("lens,splits,few", [((300, 600), 3, 4), ((256, 513), 10, 4), ((1, 257), 32, 2),
+                                             ((520, 40), 2, 21)])
+def test_half_tiles_even_splits(lens, splits, few, D, fp8):
+    """An even split of at most 128 work-groups runs every tile's pieces as
+    two of 256 rows each; with more heads it runs whole ones.  A head's rows
+    are the same bits in both, and the unsplit step's up to the order of the
+    merge's fp32 sums and one bf16 rounding."""
+    from synthgen import Workload
+    lt, x = lens
+    H = 64
+    wl = Workload("halves", 1, H, D, ((0, 24), (1, lt), (2, x), (3, 200), (3, 90)), std=1.0, seed=41)
+    print(f"[case] half tiles lens={lens} splits={splits} D={D} fp8={fp8}", flush=True)
+    inp = draw_inputs(wl)
+    L = layout_for(inp, "perref")
+    st = [t.to(DEV) for t in inp.static]
+    if fp8:
+        _, _, *cache = rc.ref_kv_prefill_fp8(L, *st, scale=wl.scale)
+    else:
+        _, _, *cache = rc.ref_kv_prefill(L, *st, scale=wl.scale)
+
+    def run(h0, h1, s):
+        lv = [t[:, :, h0:h1].contiguous().to(DEV) for t in inp.live]
+        step = rc.step_masked_attention_fp8 if fp8 else rc.step_masked_attention
+        ol, lse = step(L, *lv, *(t[:, h0:h1].contiguous() for t in cache), splits=s, scale=wl.scale, want_lse=True)
+        torch.cuda.synchronize()
+        return ol, lse
+
+    whole, half = run(0, H, splits), run(3, 3 + few, splits)
+    assert L.launch_shape(1, H, D, splits)[0] > 128 >= L.launch_shape(1, few, D, splits)[0]
+    assert torch.equal(whole[0][:, :, 3:3 + few], half[0])
+    assert torch.equal(whole[1][:, 3:3 + few], half[1])
+    one = run(3, 3 + few, 1)
+    check(half[0], f64(one[0]), f"half tiles {lens} splits={splits} D={D} fp8={fp8}")
+    check_lse(half[1], f64(one[1]), f"half tiles {lens} splits={splits}")
+
+
+@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (128, True)])
 @pytest.mark.parametrize("lens,splits", [((33, 31), 2), ((1, 64), 5), ((32, 95), 9), ((16, 520), 32),
                                          ((300, 700), rc.SPLITS_TAIL)])
 def test_split_merge_row_blocks(lens, splits, D, fp8):
