@@ -18,8 +18,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-
 #include "rc_internal.h"
 
 namespace rc {
@@ -264,20 +262,19 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
 }
 
 // A grid of 256 x 256 tiles whose last partial round is cut into smaller parts,
-// so that the round ends sooner: tiles [end[l - 1], end[l]) (logical order) run
-// in parts of level l, each level's parts after the one before, on the CUs
-// that become free.  Same bits as whole tiles.  The chip is power-bound in
-// full rounds (about 79 us each at K = 3072 with all CUs busy), so cutting only
-// recovers what a round's idle CUs do not give back in clock: 1.125 rounds of
-// N = 9216, K = 3072 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 ->
-// 185, 2.53 rounds 221 -> 218, 4.2 rounds 361 -> 336; 1.1 rounds of N = K = 1024
-// 49 -> 40 us.  The two smallest levels run on four of the work-group's waves:
-// as fast as on eight.
-constexpr int kLevels = 4;
-constexpr int kLevelM[kLevels] = {256, 256, 128, 64}, kLevelN[kLevels] = {256, 128, 128, 128};
-constexpr int level_parts(int l) { return 65536 / (kLevelM[l] * kLevelN[l]); }
+// so that the round ends sooner: tiles from `whole` on (logical order) run in
+// parts of kPartM[part] x kPartN[part], on the CUs that become free.  Same bits
+// as whole tiles.  The chip is power-bound in full rounds (about 79 us each at
+// K = 3072: MFMAs in 71% of the cycles, at 1.74 GHz), so cutting only recovers
+// what a round's idle CUs do not give back in clock: 1.125 rounds of N = 9216,
+// K = 3072 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 -> 185, 4.2
+// rounds 361 -> 336; 1.1 rounds of N = K = 1024 49 -> 40 us.  The two smaller
+// parts run on four of the work-group's waves: as fast as on eight.
+constexpr int kPartM[] = {64, 128, 256}, kPartN[] = {128, 128, 128};
+constexpr int parts_of(int part) { return 256 * 256 / (kPartM[part] * kPartN[part]); }
 struct LinCut {
-  int64_t end[kLevels];
+  int64_t whole, tiles;  // tiles run whole, and in all
+  int part;
 };
 
 __global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, const LinCut cut) {
@@ -285,29 +282,24 @@ __global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, c
   static_assert(sizeof(ring) >= size_t(kRingBytes<4, 2, 2, 4, 1, 2>), "ring");
   static_assert(sizeof(ring) >= size_t(kRingBytes<2, 2, 2, 2, 1, 4>), "ring");
   static_assert(sizeof(ring) >= size_t(kRingBytes<2, 1, 1, 4, 1, 6>), "ring");
-  int64_t i = blockIdx.x, first = 0;
-  int l = 0;
-  for (; l < kLevels - 1; ++l) {
-    const int64_t n = (cut.end[l] - first) * level_parts(l);
-    if (i < n) break;
-    i -= n;
-    first = cut.end[l];
-  }
-  const int parts = level_parts(l), across = 256 / kLevelN[l];
-  const int64_t w = lin_xcd_block(i, (cut.end[l] - first) * parts);
-  const int part = int(w % parts);
   int64_t m0;
   int n0;
-  lin_tile<256, 256>(q, first + w / parts, m0, n0);
-  m0 += part / across * kLevelM[l];
-  n0 += part % across * kLevelN[l];
+  if (int64_t(blockIdx.x) < cut.whole) {
+    lin_tile<256, 256>(q, lin_xcd_block(blockIdx.x, cut.whole), m0, n0);
+    linear_tile<4, 2, 2, 4, 1, 2, 3>(q, ring, m0, n0);
+    return;
+  }
+  const int parts = parts_of(cut.part);
+  const int64_t w = lin_xcd_block(blockIdx.x - cut.whole, (cut.tiles - cut.whole) * parts);
+  lin_tile<256, 256>(q, cut.whole + w / parts, m0, n0);
+  m0 += int(w % parts) / 2 * kPartM[cut.part];
+  n0 += int(w % parts) % 2 * 128;
   if (m0 >= q.M) return;
-  if (l >= 2 && threadIdx.x >= 256) return;  // barriers wait for the waves that remain
-  switch (l) {
-    case 0: linear_tile<4, 2, 2, 4, 1, 2, 3>(q, ring, m0, n0); break;
-    case 1: linear_tile<2, 2, 4, 2, 1, 3, 8>(q, ring, m0, n0); break;
-    case 2: linear_tile<2, 2, 2, 2, 1, 4, 8>(q, ring, m0, n0); break;
-    default: linear_tile<2, 1, 1, 4, 1, 6, 3>(q, ring, m0, n0); break;
+  if (cut.part < 2 && threadIdx.x >= 256) return;  // barriers wait for the waves that remain
+  switch (cut.part) {
+    case 0: linear_tile<2, 1, 1, 4, 1, 6, 3>(q, ring, m0, n0); break;
+    case 1: linear_tile<2, 2, 2, 2, 1, 4, 8>(q, ring, m0, n0); break;
+    default: linear_tile<2, 2, 4, 2, 1, 3, 8>(q, ring, m0, n0); break;
   }
 }
 
@@ -331,8 +323,9 @@ struct LinTile {
 };
 constexpr LinTile kLinTiles[] = {{256, 256, 71}, {256, 128, 41}, {128, 128, 25}, {64, 128, 18}, {64, 64, 12}};
 
-int pick_linear(const LinearParams& q, int64_t& best_cost) {
+int pick_linear(const LinearParams& q) {
   int best = -1;
+  int64_t best_cost = 0;
   for (int i = 0; i < 5; ++i) {
     const LinTile t = kLinTiles[i];
     if (q.N % t.bn != 0) continue;
@@ -346,31 +339,20 @@ int pick_linear(const LinearParams& q, int64_t& best_cost) {
   return best;
 }
 
-// The cheapest cut of `tiles` 256 x 256 tiles from tile `first` on: a level
-// takes its whole rounds and leaves the rest to the next, or takes everything.
-// Costs in the units of kLinTiles, of rounds next to those of other levels: the
-// parts start when CUs become free, not all at once.  The last level costs less
-// where it fills less than half of the CUs (three levels for 136 tiles over
-// whole rounds gain 1.5%; for 160, with the last round full, they lose 1%).
-constexpr int64_t kLevelCost[kLevels] = {71, 45, 30, 27};
-constexpr int64_t kLastHalfCost = 18;
-
-int64_t plan_cut(int64_t tiles, int l, int64_t first, LinCut& cut) {
-  const int64_t blocks = (tiles - first) * level_parts(l);
-  LinCut all = cut;
-  for (int i = l; i < kLevels; ++i) all.end[i] = tiles;
-  const int64_t all_cost = l == kLevels - 1 && 2 * blocks <= kCUs ? (blocks > 0 ? kLastHalfCost : 0)
-                                                                  : (blocks + kCUs - 1) / kCUs * kLevelCost[l];
-  if (l == kLevels - 1 || blocks % kCUs == 0) {
-    cut = all;
-    return all_cost;
-  }
-  const int64_t rounds = blocks / kCUs;
-  LinCut sub = cut;
-  sub.end[l] = first + rounds * kCUs / level_parts(l);
-  const int64_t sub_cost = rounds * kLevelCost[l] + plan_cut(tiles, l + 1, sub.end[l], sub);
-  cut = sub_cost < all_cost ? sub : all;
-  return std::min(sub_cost, all_cost);
+// The cut of a call that would run more than one round of 256 x 256 tiles: the
+// smallest parts that still fit one round.  A last round more than half full
+// stays whole, for its parts would need two rounds (256 x 128 and smaller ones
+// for 136 to 160 of 256 tiles measured within 1% of whole tiles either way,
+// for 176 2-7% slower).
+bool plan_cut(const LinearParams& q, LinCut& cut) {
+  if (q.N % 256 != 0) return false;
+  cut.tiles = (q.M + 255) / 256 * (q.N / 256);
+  cut.whole = cut.tiles / kCUs * kCUs;
+  const int64_t rest = cut.tiles - cut.whole;
+  if (cut.whole == 0 || rest == 0) return false;
+  for (cut.part = 0; cut.part < 3; ++cut.part)
+    if (rest * parts_of(cut.part) <= kCUs) return true;
+  return false;
 }
 
 }  // namespace
@@ -378,17 +360,13 @@ int64_t plan_cut(int64_t tiles, int l, int64_t first, LinCut& cut) {
 int launch_linear(const LinearParams& q, void* stream) {
   if (q.M == 0) return 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int64_t cost = 0;
-  const int tile = pick_linear(q, cost);
-  const int64_t tiles = q.N % 256 == 0 ? (q.M + 255) / 256 * (q.N / 256) : 0;
-  LinCut cut{};
-  if (tiles > kCUs && plan_cut(tiles, 0, 0, cut) < cost) {
-    int64_t blocks = 0;
-    for (int l = 0; l < kLevels; ++l) blocks += (cut.end[l] - (l ? cut.end[l - 1] : 0)) * level_parts(l);
+  LinCut cut;
+  if (plan_cut(q, cut)) {
+    const int64_t blocks = cut.whole + (cut.tiles - cut.whole) * parts_of(cut.part);
     hipLaunchKernelGGL(linear_cut_kernel, dim3(blocks), dim3(512), 0, s, q, cut);
     return int(hipGetLastError());
   }
-  switch (tile) {
+  switch (pick_linear(q)) {
     case 0: launch_tile<4, 2, 2, 4, 1, 2, 3>(q, s); break;
     case 1: launch_tile<2, 2, 4, 2, 1, 3, 8>(q, s); break;
     case 2: launch_tile<2, 2, 2, 2, 1, 4, 8>(q, s); break;

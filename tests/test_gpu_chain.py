@@ -175,8 +175,7 @@ def test_linear_every_tile(M, N, K, resid):
 
 
 # More than one round of 256 x 256 tiles: the last partial one in 64 x 128,
-# 128 x 128 or 256 x 128 parts, in 256 x 128 and 64 x 128 ones, or whole; the
-# last 64-row parts lie past M.  Every row against the same rows in calls of
+# 128 x 128 or 256 x 128 parts, or whole; the last 64-row parts lie past M.  Every row against the same rows in calls of
 # their own (at most 64 tiles, one size), sampled rows against the oracle.
 @pytest.mark.parametrize("m_tiles,K,resid", [(33, 64, True), (36, 192, False), (40, 64, True), (44, 64, False),
                                              (48, 128, False), (49, 64, True), (53, 64, False), (71, 64, False)])
