@@ -9,7 +9,7 @@
 // Work-group = 8 waves of 64 lanes, one work-group and two waves per SIMD on
 // each CU.  A wave owns QB blocks of 32 query rows (two in the step over
 // either cache, the prefill and the full recompute: BM = 512; one in the
-// balanced schedule: BM = 256).
+// balanced schedule and in the others' tiles of at most 256 rows: BM = 256).
 // Per 64-key tile:
 //   S^T = K Q^T     v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = the
 //                   wave's Q rows held in registers for the whole kernel; each
@@ -34,7 +34,7 @@
 //
 // With two query blocks per wave a tile is computed as two 32-key sub-tiles,
 // and the two waves of each SIMD run half a phase apart (the ping-pong ring):
-// one issues MFMAs while the other does its softmax.  With one block per wave
+// one issues MFMAs while the other does its softmax.  In the balanced schedule
 // every wave loads and computes whole tiles behind one barrier per tile.
 //
 // Over the FP8 cache (the kF8 instantiation) the fresh key ranges run through
@@ -1415,8 +1415,9 @@ __global__ __launch_bounds__(256) void clear_kernel(float* a, int n) {
 // A tile, or what is left of one, of at most 256 rows runs with one 32-row
 // block per wave: 0.6 of a whole tile's time, since
 // every K and V^T fragment then feeds one MFMA and the fragment reads take as
-// many LDS cycles as the MFMAs.  The last p.half_tiles tiles run as two
-// work-groups of 256 rows each, on CUs that would be idle (half_tiles()).
+// many LDS cycles as the MFMAs.  The last p.half_tiles tiles (in an even split
+// all, and each of their pieces) run as two work-groups of 256 rows each, on
+// CUs that would be idle (half_tiles()).
 template <int D, bool kSplit, bool kF8>
 __global__ __launch_bounds__(kThreads, 2) void attn_fwd_kernel(const Params p) {
   static_assert(kQBFp8 == kQBPlain, "one tile size over either cache");
