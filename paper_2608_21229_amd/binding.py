@@ -4,6 +4,11 @@ Argument marshalling only: tensors are passed as device pointers and the
 current torch stream as a hipStream_t; every step of the computation runs in
 the library's HIP kernels.  torch supplies device memory and streams.
 
+``stream=`` runs a call on that stream instead: as everywhere in torch, the
+caller orders it after the work that made the inputs and before the reads of
+the outputs, and keeps the tensors it passes until the call's kernels are
+done.  What the call allocates itself lives as long as they need it.
+
 Loading fails loudly if the library has not been built
 (``python -m paper_2608_21229_amd.build``): there is no fallback path.
 """
@@ -229,6 +234,29 @@ def _call(fn, dev, stream, *args):
     _check(fn(*args, torch._C._cuda_getCurrentRawStream(dev.index) if stream is None else stream.cuda_stream))
 
 
+def _on(stream, dev):
+    """Context in which the caller's stream is the current one."""
+    cuda = _torch().cuda
+    return cuda.stream(stream if isinstance(stream, cuda.Stream)
+                       else cuda.ExternalStream(stream.cuda_stream, device=dev))
+
+
+def _empty(shape, dtype, dev, stream, returned=True):
+    """Memory that a call allocates for itself.  With a stream given it is that
+    stream's: memory of the current stream would be free for the current
+    stream's next allocation as soon as its tensor is dropped (a workspace: on
+    return), while the call's kernels still use it.  A returned tensor is
+    marked as used on the current stream too, where the caller reads it."""
+    torch = _torch()
+    if stream is None:
+        return torch.empty(shape, dtype=dtype, device=dev)
+    with _on(stream, dev):
+        t = torch.empty(shape, dtype=dtype, device=dev)
+    if returned:
+        t.record_stream(torch.cuda.current_stream(dev))
+    return t
+
+
 def _inputs(q, k, v):
     """Q/K/V: bf16 tensors of one shape on one GPU; returns that device.  The
     library takes raw device pointers, so a host tensor must never reach it."""
@@ -272,13 +300,13 @@ def ref_kv_prefill(layout: Layout, q, k, v, o=None, lse=None, k_cache=None, v_ca
     ts = _tok_stride(q, k, v)
     nc = layout.rows(ROWS_CACHED)
     if o is None:
-        o = torch.empty((B, N, H, D), dtype=torch.bfloat16, device=q.device)
+        o = _empty((B, N, H, D), torch.bfloat16, dev, stream)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
+        lse = _empty((B, H, N), torch.float32, dev, stream)
     if k_cache is None:
-        k_cache = torch.empty((B, H, nc, D), dtype=torch.bfloat16, device=q.device)
+        k_cache = _empty((B, H, nc, D), torch.bfloat16, dev, stream)
     if v_cache is None:
-        v_cache = torch.empty((B, H, nc, D), dtype=torch.bfloat16, device=q.device)
+        v_cache = _empty((B, H, nc, D), torch.bfloat16, dev, stream)
     _expect(o, (B, N, H, D), "torch.bfloat16", "o")
     _expect(lse, (B, H, N), "torch.float32", "lse")
     _expect(k_cache, (B, H, nc, D), "torch.bfloat16", "k_cache")
@@ -303,9 +331,9 @@ def step_masked_attention(layout: Layout, q, k, v, k_cache, v_cache, o=None, lse
     scale = 1.0 / math.sqrt(D) if scale is None else scale
     ts = _tok_stride(q, k, v)
     if o is None:
-        o = torch.empty((B, N, H, D), dtype=torch.bfloat16, device=q.device)
+        o = _empty((B, N, H, D), torch.bfloat16, dev, stream)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
+        lse = _empty((B, H, N), torch.float32, dev, stream)
     nc = layout.rows(ROWS_CACHED)
     _expect(o, (B, N, H, D), "torch.bfloat16", "o")
     _expect(lse, (B, H, N), "torch.float32", "lse")
@@ -313,7 +341,7 @@ def step_masked_attention(layout: Layout, q, k, v, k_cache, v_cache, o=None, lse
     _expect(v_cache, (B, H, nc, D), "torch.bfloat16", "v_cache")
     need = layout.workspace_bytes(B, H, D, splits)
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+        workspace = _empty(need, torch.uint8, dev, stream, returned=False)
     _same_device(dev, o=o, lse=lse, k_cache=k_cache, v_cache=v_cache, workspace=workspace if need else None)
     _call(lib().rc_step_masked_attention, dev, stream, ctypes.byref(layout.c), B, H, D, scale, q.data_ptr(),
           k.data_ptr(), v.data_ptr(), ts, _ptr(k_cache), _ptr(v_cache), o.data_ptr(), _ptr(lse), splits,
@@ -359,14 +387,14 @@ def full_attention(layout: Layout, q, k, v, o=None, lse=None, scale: Optional[fl
     scale = 1.0 / math.sqrt(D) if scale is None else scale
     ts = _tok_stride(q, k, v)
     if o is None:
-        o = torch.empty((B, N, H, D), dtype=torch.bfloat16, device=q.device)
+        o = _empty((B, N, H, D), torch.bfloat16, dev, stream)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
+        lse = _empty((B, H, N), torch.float32, dev, stream)
     _expect(o, (B, N, H, D), "torch.bfloat16", "o")
     _expect(lse, (B, H, N), "torch.float32", "lse")
     _same_device(dev, o=o, lse=lse)
     need = layout.full_workspace_bytes(B, H, D) if last_round_split else 0
-    ws = torch.empty(need, dtype=torch.uint8, device=q.device) if need else None
+    ws = _empty(need, torch.uint8, dev, stream, returned=False) if need else None
     _call(lib().rc_full_attention_ws, dev, stream, ctypes.byref(layout.c), B, H, D, scale, q.data_ptr(), k.data_ptr(),
           v.data_ptr(), ts, o.data_ptr(), _ptr(lse), _ptr(ws), need)
     return o, lse
@@ -393,7 +421,7 @@ def linear(a, w, residual=None, out=None, stream=None):
         raise ValueError(f"w must be a contiguous bf16 [N, {K}] tensor, got {str(w.dtype)} {tuple(w.shape)}")
     N = w.shape[0]
     if out is None:
-        out = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
+        out = _empty((M, N), torch.bfloat16, dev, stream)
     for name, t in (("out", out), ("residual", residual)):
         if t is not None and t.shape != (M, N):
             raise ValueError(f"{name} must have shape {(M, N)}, got {tuple(t.shape)}")
@@ -425,15 +453,15 @@ def ref_kv_prefill_fp8(layout: Layout, q, k, v, o=None, lse=None, k_cache8=None,
     ts = _tok_stride(q, k, v)
     ks, vs, ss = fp8_cache_shapes(layout, B, H, D)
     if o is None:
-        o = torch.empty((B, N, H, D), dtype=torch.bfloat16, device=dev)
+        o = _empty((B, N, H, D), torch.bfloat16, dev, stream)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=dev)
+        lse = _empty((B, H, N), torch.float32, dev, stream)
     if k_cache8 is None:
-        k_cache8 = torch.empty(ks, dtype=torch.uint8, device=dev)
+        k_cache8 = _empty(ks, torch.uint8, dev, stream)
     if v_cache8 is None:
-        v_cache8 = torch.empty(vs, dtype=torch.uint8, device=dev)
+        v_cache8 = _empty(vs, torch.uint8, dev, stream)
     if kv_scale is None:
-        kv_scale = torch.empty(ss, dtype=torch.float32, device=dev)
+        kv_scale = _empty(ss, torch.float32, dev, stream)
     _expect(o, (B, N, H, D), "torch.bfloat16", "o")
     _expect(lse, (B, H, N), "torch.float32", "lse")
     _expect(k_cache8, ks, "torch.uint8", "k_cache8")
@@ -458,9 +486,9 @@ def step_masked_attention_fp8(layout: Layout, q, k, v, k_cache8, v_cache8, kv_sc
     ts = _tok_stride(q, k, v)
     ks, vs, ss = fp8_cache_shapes(layout, B, H, D)
     if o is None:
-        o = torch.empty((B, N, H, D), dtype=torch.bfloat16, device=dev)
+        o = _empty((B, N, H, D), torch.bfloat16, dev, stream)
     if lse is None and want_lse:
-        lse = torch.empty((B, H, N), dtype=torch.float32, device=dev)
+        lse = _empty((B, H, N), torch.float32, dev, stream)
     _expect(o, (B, N, H, D), "torch.bfloat16", "o")
     _expect(lse, (B, H, N), "torch.float32", "lse")
     _expect(k_cache8, ks, "torch.uint8", "k_cache8")
@@ -468,7 +496,7 @@ def step_masked_attention_fp8(layout: Layout, q, k, v, k_cache8, v_cache8, kv_sc
     _expect(kv_scale, ss, "torch.float32", "kv_scale")
     need = layout.workspace_bytes(B, H, D, splits) if splits != SPLITS_BALANCED else 0
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = _empty(need, torch.uint8, dev, stream, returned=False)
     _same_device(dev, o=o, lse=lse, k_cache8=k_cache8, v_cache8=v_cache8, kv_scale=kv_scale,
                  workspace=workspace if need else None)
     _call(lib().rc_step_masked_attention_fp8, dev, stream, ctypes.byref(layout.c), B, H, D, scale, q.data_ptr(),

@@ -22,10 +22,12 @@ with per-(batch, head) scales (``ref_kv_prefill_fp8`` /
 
 Marshalling only: every multiply-add runs in librefcache.  Work buffers come
 from torch's allocator; ``collect`` (a list) receives a copy of the hidden
-state after each layer.
+state after each layer.  With ``stream`` given, everything that a call
+allocates, copies and launches is that stream's.
 """
 from __future__ import annotations
 
+import contextlib
 import math
 from typing import List, Optional, Sequence, Tuple
 
@@ -57,6 +59,17 @@ class Chain:
     def layers(self) -> int:
         return len(self.w_qkv)
 
+    @contextlib.contextmanager
+    def _scope(self, stream, dev):
+        """Makes the caller's stream the current one; yields a function that
+        marks tensors to be returned as used on the stream that was current."""
+        if stream is None:
+            yield lambda *ts: None
+            return
+        caller = rcb._torch().cuda.current_stream(dev)
+        with rcb._on(stream, dev):
+            yield lambda *ts: [t.record_stream(caller) for t in ts]
+
     def _buffers(self, h, rows_kind: int):
         torch = rcb._torch()
         if h.dim() != 3 or h.shape[2] != self.C:
@@ -75,6 +88,13 @@ class Chain:
         return t[:, :, 0], t[:, :, 1], t[:, :, 2]
 
     def _run(self, h, rows_kind, attend, collect: Optional[List], last_out: bool = True, stream=None):
+        with self._scope(stream, h.device) as returned:
+            n = len(collect) if collect is not None else 0
+            out = self._layers(h, rows_kind, attend, collect, last_out, stream)
+            returned(out, *(collect[n:] if collect is not None else ()))
+            return out
+
+    def _layers(self, h, rows_kind, attend, collect, last_out, stream):
         B, N, qkv, o, work = self._buffers(h, rows_kind)
         src = h.reshape(B * N, self.C)
         for l in range(self.layers):
@@ -106,7 +126,10 @@ class Chain:
         Fills and returns one cache entry per layer (see ``new_caches``).  The static
         rows' output projection of the last layer is skipped (nobody reads
         it) unless ``collect`` asks for the hidden states."""
-        caches = self.new_caches(h_static.shape[0], h_static.device) if caches is None else caches
+        if caches is None:
+            with self._scope(stream, h_static.device) as returned:
+                caches = self.new_caches(h_static.shape[0], h_static.device)
+                returned(*(t for entry in caches for t in entry))
         if len(caches) != self.layers:
             raise ValueError(f"need {self.layers} cache entries, got {len(caches)}")
 
@@ -126,10 +149,9 @@ class Chain:
         Returns the live rows' hidden state after the last layer."""
         if len(caches) != self.layers:
             raise ValueError(f"need {self.layers} cache entries, got {len(caches)}")
-        torch = rcb._torch()
         B = h_live.shape[0]
         need = self.layout.workspace_bytes(B, self.H, self.D, splits)
-        ws = torch.empty(need, dtype=torch.uint8, device=h_live.device) if need else None
+        ws = rcb._empty(need, rcb._torch().uint8, h_live.device, stream, returned=False) if need else None
 
         def attend(l, q, k, v, o):
             if self.cache == "fp8":
