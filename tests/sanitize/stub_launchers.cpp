@@ -17,6 +17,7 @@
 namespace {
 
 long g_launches = 0;
+long g_runs = 0;  // runs of the last copy table
 
 [[noreturn]] void fail(const char* what, long a, long b) {
   fprintf(stderr, "stub launcher: broken schedule: %s (%ld, %ld)\n", what, a, b);
@@ -88,8 +89,11 @@ void check_copy(const rc::CopySeg* seg, int n_copy, int32_t n_cached) {
   for (int i = 0; i < n_copy; ++i) {
     REQUIRE(seg[i].len >= 1 && seg[i].src_row0 >= 0, i, seg[i].len);
     REQUIRE(seg[i].dst_row0 == dst, i, seg[i].dst_row0);
+    // runs that follow each other in the source as in the cache are one
+    REQUIRE(i == 0 || seg[i].src_row0 > seg[i - 1].src_row0 + seg[i - 1].len, i, seg[i].src_row0);
     dst += seg[i].len;
   }
+  g_runs = n_copy;
   REQUIRE(dst == n_cached, dst, n_cached);
 }
 
@@ -180,3 +184,4 @@ int scratch_address(void** ptr) {
 }  // namespace rc
 
 extern "C" long rc_stub_launches(void) { return g_launches; }
+extern "C" long rc_stub_copy_runs() { return g_runs; }
