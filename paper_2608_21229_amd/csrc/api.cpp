@@ -251,8 +251,8 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   if (n_cached > 0) {
     // amax work-groups at the end of the attention grid take the (batch,
     // head)s that fit on the CUs its partial last round leaves free
-    const CopyPlan cpl = plan_copy_tail(p, n_cached);
-    c.bh0 = cpl.blocks > 0 ? int32_t(cpl.rows / n_cached) : 0;
+    const CopyPlan cpl = plan_amax_tail(p, n_cached, D);
+    c.bh0 = int32_t(cpl.rows / n_cached);
     CopyTail& t = p.cp;
     t.B = B;
     t.H = H;
@@ -267,7 +267,7 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
       t.n_copy = c.n_copy;
       for (int i = 0; i < n_copy; ++i) t.seg[i] = seg[i];
       t.blocks = cpl.blocks;
-      t.rows = c.bh0 * c.n_cached;
+      t.rows = int32_t(cpl.rows);
       t.amax = kv_scale;
       RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + cpl.blocks, "prefill attention"));
     } else {

@@ -10,15 +10,18 @@
 // computes.  Dividing by a power of two is exact, so a code depends on x alone,
 // and code * s is exact in bf16.
 //
-// Three launches after the prefill's attention: per-(b, h) amax (work-group
-// maxima, then one atomic max per work-group and tensor: the result does not
-// depend on the order), the quantising store of K and V, and the scales
-// written over the amax values.  The attention launch clears the accumulators
-// and, on the CUs that its partial last round leaves idle, takes the amax of
-// the first c.bh0 (batch, head)s (amax_tail); when that is all of them, the
-// amax launch is left out.  (References of 3 x 4096 and 3 x 1024 tokens, 24
-// heads: the amax launch took 42 us and the clearing one 5, now neither;
-// prefill 693 -> 653 us.)
+// Up to three launches after the prefill's attention: per-(b, h) amax
+// (work-group maxima, then one atomic max per work-group and tensor: the result
+// does not depend on the order), the quantising store of K and V, and the
+// scales written over the amax values.  Where the CUs that the attention's
+// partial last round leaves idle can take the amax of every (batch, head), or
+// of enough of them to shorten the amax launch (plan_amax_tail), work-groups at
+// the end of the attention grid take the first c.bh0 (amax_tail), a clear
+// kernel goes before the attention, and the amax launch takes the rest or is
+// left out.  Without such work-groups the attention launch itself clears the
+// accumulators.  (References of 3 x 4096 and 3 x 1024 tokens, 24 heads: the
+// amax launch took 42 us beside a clear kernel of 5; now the clear kernel alone.
+// Prefill 693 -> 653 us.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -276,8 +276,8 @@ bool per_batch_launches(const Params& p) {
 // 100 or more at D = 128 with 512-row tiles, and larger settings were no
 // better overall).  The model stops at kMaxModelWGs work-groups, where the
 // store is a small part of the launch.  The FP8 prefill's amax work-groups
-// follow the same plan (32, 48, 64, 128 rows per tile time: 672, 652, 653, 725
-// us with references of 3 x 4096 and 3 x 1024 tokens).
+// follow the same plan (plan_amax_tail; 32, 48, 64, 128 rows per tile time:
+// 672, 652, 653, 725 us with references of 3 x 4096 and 3 x 1024 tokens).
 namespace {
 constexpr int64_t kCopyRowsPerTile = 64;
 constexpr int64_t kTileOverhead = 2;
@@ -340,6 +340,28 @@ CopyPlan plan_copy_tail(const Params& p, int64_t n_cached) {
   }
   const int64_t rows = std::min(R, c * kCopyRowsPerTile * win[size_t(c - 1)]);
   return CopyPlan{int32_t(c), rows};
+}
+
+CopyPlan plan_amax_tail(const Params& p, int64_t n_cached, int32_t D) {
+  // Whole (batch, head)s only.  All of them save the amax launch.  Some of
+  // them shorten it only where it is bound by bandwidth: below about 100 MB of
+  // K and V it takes about 20 us however many heads are left to it, so they
+  // would only lengthen the attention launch; and the plan's windows have to
+  // be long, for amax work-groups start later than its model says.
+  // Prefill us with none and with some of the heads in the attention launch:
+  // two entries of 24 heads, D = 64, 10 x 128 tokens (17 MB, window 3 tile
+  // times) 43 and 63; 40 heads, D = 64, 3 x 1024 (32 MB, 3) 70 and 90; 24
+  // heads, D = 128, 3 x 1519 (57 MB, 24) 117 and 130; 40 heads, D = 128, 5 x
+  // 4096 (421 MB, 64) 1652 and 1600.
+  constexpr int64_t kMinBytes = 96 << 20, kMinWindow = 32;
+  const CopyPlan none{0, 0};
+  CopyPlan c = plan_copy_tail(p, n_cached);
+  if (c.blocks == 0) return none;
+  const int64_t heads = int64_t(p.B) * p.H, taken = c.rows / n_cached;
+  if (taken < heads && (heads * n_cached * D * 4 < kMinBytes || c.rows < c.blocks * kMinWindow * kCopyRowsPerTile))
+    return none;
+  c.rows = taken * n_cached;
+  return taken > 0 ? c : none;
 }
 
 int32_t last_round_tiles(Params& p) {

@@ -198,6 +198,9 @@ struct CopyPlan {
   int64_t rows;
 };
 CopyPlan plan_copy_tail(const Params& p, int64_t n_cached);
+// The FP8 prefill's amax work-groups: the same for the whole (batch, head)s
+// whose largest magnitudes they take (rows is a multiple of n_cached).
+CopyPlan plan_amax_tail(const Params& p, int64_t n_cached, int32_t D);
 
 void set_error(const char* fmt, ...);
 

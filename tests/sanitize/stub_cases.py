@@ -71,3 +71,25 @@ def test_copy_table_has_one_run_per_stretch_of_rows(segs, mask, runs):
     L = rc.Layout(segs, mask)
     assert _prefill(L) == rc.RC_OK and stub("rc_stub_copy_runs") == runs
     assert _prefill_fp8(L) == rc.RC_OK and stub("rc_stub_copy_runs") == runs
+
+
+HEAD = [(0, 64), (1, 64), (2, 256)]
+
+
+@pytest.mark.parametrize("refs,mask,B,H,D,heads", [
+    ([128] * 10, "perref", 2, 24, 64, 0),         # 36 heads would fit on the idle CUs: 17 MB, short windows
+    ([128] * 10, "perref", 2, 24, 128, 0),
+    ([1024] * 3, "perref", 1, 40, 64, 0),         # 14 of 40
+    ([1519] * 3, "perref", 1, 24, 128, 0),        # 13 of 24: 57 MB
+    ([4096] * 8, "perref", 1, 24, 128, 0),        # 1 of 24: 403 MB, but windows of three tile times
+    ([128] * 20, "paper", 1, 24, 64, 0),          # 8 of 24: long windows, 16 MB
+    ([4096] * 5, "perref", 1, 24, 128, 12),       # 252 MB, windows of 64
+    ([4096] * 5, "perref", 1, 40, 128, 38),
+    ([4096] * 3, "perref", 1, 24, 128, 24),       # all of them
+    ([100] * 3, "perref", 1, 24, 64, 24),         # all, however small
+])
+def test_amax_work_groups_take_all_heads_or_many(refs, mask, B, H, D, heads):
+    """The FP8 prefill's attention launch takes the amax of every head, or of
+    some where that shortens the amax launch, or of none."""
+    assert _prefill_fp8(rc.Layout(HEAD + [(3, n) for n in refs], mask), B, H, D) == rc.RC_OK
+    assert stub("rc_stub_amax_heads") == heads

@@ -18,6 +18,7 @@ namespace {
 
 long g_launches = 0;
 long g_runs = 0;  // runs of the last copy table
+long g_heads = -1;  // (batch, head)s whose amax the last FP8 prefill's attention launch takes
 
 [[noreturn]] void fail(const char* what, long a, long b) {
   fprintf(stderr, "stub launcher: broken schedule: %s (%ld, %ld)\n", what, a, b);
@@ -162,6 +163,8 @@ int launch_cache_store_fp8(const CacheStore8Params& c, void*) {
   REQUIRE(c.k_src && c.v_src && c.k_dst && c.v_dst && c.kv_scale, 0, 0);
   REQUIRE(c.n_cached <= kFp8MaxKeys, c.n_cached, 0);
   check_copy(c.seg, c.n_copy, c.n_cached);
+  REQUIRE(c.bh0 >= 0 && c.bh0 <= c.B * c.H, c.bh0, c.B * c.H);
+  g_heads = c.bh0;
   ++g_launches;
   return 0;
 }
@@ -185,3 +188,4 @@ int scratch_address(void** ptr) {
 
 extern "C" long rc_stub_launches(void) { return g_launches; }
 extern "C" long rc_stub_copy_runs() { return g_runs; }
+extern "C" long rc_stub_amax_heads() { return g_heads; }
