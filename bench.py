@@ -225,7 +225,7 @@ def extras(torch, rc, wl, gen, dev, static, live, step_ms_main):
         ws = torch.empty(max(wsb, 16), dtype=torch.uint8, device=dev)
         ms = time_calls(torch, lambda: rc.step_masked_attention(L, ql, kl, vl, kc, vc, o=o, splits=spr,
                                                                 workspace=ws if wsb else None, scale=wl.scale))
-        share[name] = {"splits": spr, "work_groups": L.launch_shape(B, Hs, D, spr)[0], "step_ms": ms,
+        share[name] = {"splits": spr, "work_groups": L.work_groups(rc.ENTRY_STEP, B, Hs, D, spr), "step_ms": ms,
                        "tflops": flop_pair * B * Hs / (ms * 1e-3) / 1e12}
     out["one_gpu_head_share"] = share
     del ql, kl, vl, kc, vc, o
@@ -394,7 +394,10 @@ def main():
     flop_pre = 4.0 * D * H * B * pairs_pre
     flop_request = LAYERS * (flop_pre + T * flop_step)
     splits = args.splits if args.splits else L.auto_splits(B, H, D)
-    step_wgs, step_bm, step_splits = L.launch_shape(B, H, D, splits, args.fp8_cache)
+    planned, step_bm, step_splits = L.launch_shape(B, H, D, splits, args.fp8_cache)
+    step_wgs = L.work_groups(rc.ENTRY_STEP, B, H, D, splits, args.fp8_cache)
+    if step_wgs == 2 * planned:  # every tile runs as two halves
+        step_bm //= 2
 
     # ---- inputs, resident in HBM before timing
     gen = torch.Generator(device=dev)

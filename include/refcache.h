@@ -194,6 +194,18 @@ int32_t rc_step_auto_splits(const rc_layout* L, int32_t B, int32_t H, int32_t D)
 rc_status rc_step_launch_shape(const rc_layout* L, int32_t B, int32_t H, int32_t D, int32_t splits, int32_t fp8,
                                int64_t* work_groups, int32_t* rows_per_wg, int32_t* splits_used);
 
+/* Work-groups that an attention call launches, for occupancy: the counts of
+ * rc_step_launch_shape and rc_prefill_launch_plan with a query tile or piece
+ * that runs as two work-groups of half its rows counted twice.
+ *   entry   RC_ENTRY_PREFILL (without the copy work-groups), RC_ENTRY_STEP or
+ *           RC_ENTRY_FULL
+ *   splits  as rc_step_launch_shape; the prefill: 1; the full recompute: 1, or
+ *           RC_SPLITS_LAST_ROUND with the workspace that lets it split
+ *   fp8     1: over the FP8 cache (prefill and step)
+ * Host only; an rc_status (< 0) on invalid input. */
+int64_t rc_attention_work_groups(const rc_layout* L, int32_t entry, int32_t B, int32_t H, int32_t D, int32_t splits,
+                                 int32_t fp8);
+
 /* Launch plan of rc_ref_kv_prefill (bf16 cache), for reports and tests:
  * *attn_wgs attention work-groups over all launches (one per query tile, two
  * of half the rows counting once),

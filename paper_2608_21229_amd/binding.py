@@ -76,6 +76,7 @@ SIGNATURES = {
                                                 _vp, _i32, _vp]),
     "rc_step_launch_shape": (_i32, [_PL, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(_i64),
                                     ctypes.POINTER(_i32), ctypes.POINTER(_i32)]),
+    "rc_attention_work_groups": (_i64, [_PL, _i32, _i32, _i32, _i32, _i32, _i32]),
     "rc_full_attention_ws": (_i32, [_PL, _i32, _i32, _i32, _f32, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _sz, _vp]),
     "rc_full_workspace_bytes": (_sz, [_PL, _i32, _i32, _i32]),
     "rc_prefill_launch_plan": (_i32, [_PL, _i32, _i32, _i32, ctypes.POINTER(_i64), ctypes.POINTER(_i32),
@@ -155,11 +156,20 @@ class Layout:
 
     def launch_shape(self, B: int, H: int, D: int, splits: int = 0, fp8: bool = False):
         """(work-groups, query rows per work-group, resolved splits) of the
-        step's attention kernel."""
+        step's attention kernel, a tile run as two halves counted once
+        (``work_groups`` counts what is launched)."""
         wg, bm, sp = ctypes.c_int64(), ctypes.c_int32(), ctypes.c_int32()
         _check(lib().rc_step_launch_shape(ctypes.byref(self.c), B, H, D, splits, int(fp8), ctypes.byref(wg),
                                           ctypes.byref(bm), ctypes.byref(sp)))
         return wg.value, bm.value, sp.value
+
+    def work_groups(self, entry: int, B: int, H: int, D: int, splits: int = 1, fp8: bool = False) -> int:
+        """Work-groups that an attention call launches (ENTRY_*), tiles run as
+        two halves counted twice; see rc_attention_work_groups."""
+        n = lib().rc_attention_work_groups(ctypes.byref(self.c), entry, B, H, D, splits, int(fp8))
+        if n < 0:
+            _check(int(n))
+        return int(n)
 
     def full_workspace_bytes(self, B: int, H: int, D: int) -> int:
         """Workspace of the full recompute's last-round split (0: no split)."""

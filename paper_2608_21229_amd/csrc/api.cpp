@@ -115,6 +115,32 @@ void fill_common(Params& p, int32_t B, int32_t H, float scale) {
 namespace rc {
 namespace {
 
+// The prefill's schedule: query tiles and key ranges, the copy work-groups
+// (amax work-groups for the FP8 cache) and the cache rows they take, in p
+// (p.B and p.H set by the caller).
+rc_status plan_prefill(const rc_layout* L, int32_t D, bool fp8, Params& p) {
+  p.bm = rows_per_wg(kQBPlain);
+  RC_TRY(plan(L, RC_ENTRY_PREFILL, p));
+  const int64_t n_cached = count_cached_rows(L);
+  const CopyPlan c = fp8 ? plan_amax_tail(p, n_cached, D) : plan_copy_tail(p, n_cached);
+  p.cp.blocks = c.blocks;
+  p.cp.rows = int32_t(c.rows);
+  p.half_tiles = half_tiles(p);
+  return RC_OK;
+}
+
+// The full recompute's schedule; last_round: with the workspace that lets it
+// split the grid's partial last round.
+rc_status plan_full(const rc_layout* L, bool last_round, Params& p) {
+  p.bm = rows_per_wg(kQBPlain);
+  RC_TRY(plan(L, RC_ENTRY_FULL, p));
+  if (last_round) p.lr_tiles = last_round_tiles(p);
+  p.splits = p.lr_tiles > 0 ? 2 : 1;
+  if (p.lr_tiles == 0) p.tail_num = 0;
+  p.half_tiles = half_tiles(p);
+  return RC_OK;
+}
+
 // The prefill of both cache formats: static-row attention, then the bf16 cache
 // store or the FP8 quantising store.
 rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, float scale, const void* q_static,
@@ -152,8 +178,7 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   Params p;
   memset(&p, 0, sizeof p);
   fill_common(p, B, H, scale);
-  p.bm = rows_per_wg(kQBPlain);
-  RC_TRY(plan(L, RC_ENTRY_PREFILL, p));
+  RC_TRY(plan_prefill(L, D, fp8, p));
   RC_TRY(check_grid(p));
   p.q = static_cast<const uint16_t*>(q_static);
   p.q_st = tok_stride;
@@ -205,9 +230,8 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
     // Copy work-groups at the end of the attention grid take the cache rows
     // that fit on the CUs its partial last round leaves free; the store
     // kernel (one thread per 16-byte granule, 256 per work-group) the rest.
-    const CopyPlan cpl = plan_copy_tail(p, n_cached);
-    if (cpl.blocks > 0) {
-      CopyTail& t = p.cp;
+    CopyTail& t = p.cp;
+    if (t.blocks > 0) {
       t.k_src = c.k_src;
       t.v_src = c.v_src;
       t.k_dst = c.k_dst;
@@ -219,13 +243,10 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
       t.n_cached = c.n_cached;
       t.n_copy = c.n_copy;
       for (int i = 0; i < n_copy; ++i) t.seg[i] = seg[i];
-      t.blocks = cpl.blocks;
-      t.rows = int32_t(cpl.rows);
-      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + cpl.blocks, "prefill attention"));
+      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + t.blocks, "prefill attention"));
     }
-    p.half_tiles = half_tiles(p);
-    c.row0 = cpl.rows;
-    const int64_t rest = int64_t(B) * H * n_cached - cpl.rows;
+    c.row0 = t.rows;
+    const int64_t rest = int64_t(B) * H * n_cached - t.rows;
     RC_TRY(check_blocks((rest * (D / 8) + 255) / 256, "cache store"));
     RC_TRY(hip_status(launch_attention(p, D, stream), "prefill attention launch"));
     if (rest > 0) RC_TRY(hip_status(launch_cache_store(c, stream), "cache store launch"));
@@ -251,9 +272,8 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
   if (n_cached > 0) {
     // amax work-groups at the end of the attention grid take the (batch,
     // head)s that fit on the CUs its partial last round leaves free
-    const CopyPlan cpl = plan_amax_tail(p, n_cached, D);
-    c.bh0 = int32_t(cpl.rows / n_cached);
     CopyTail& t = p.cp;
+    c.bh0 = t.rows / c.n_cached;
     t.B = B;
     t.H = H;
     if (c.bh0 > 0) {
@@ -266,15 +286,12 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
       t.n_cached = c.n_cached;
       t.n_copy = c.n_copy;
       for (int i = 0; i < n_copy; ++i) t.seg[i] = seg[i];
-      t.blocks = cpl.blocks;
-      t.rows = int32_t(cpl.rows);
       t.amax = kv_scale;
-      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + cpl.blocks, "prefill attention"));
+      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + t.blocks, "prefill attention"));
     } else {
       p.amax_clear = kv_scale;
     }
   }
-  p.half_tiles = half_tiles(p);
   RC_TRY(check_blocks(int64_t(B) * H, "FP8 cache store"));
   RC_TRY(check_blocks((int64_t(B) * H * n_cached * (D / 8) + 255) / 256, "FP8 cache store"));
   RC_TRY(hip_status(launch_attention(p, D, stream), "prefill attention launch"));
@@ -475,12 +492,10 @@ rc_status rc_prefill_launch_plan(const rc_layout* L, int32_t B, int32_t H, int32
   Params p;
   memset(&p, 0, sizeof p);
   fill_common(p, B, H, 1.0f);
-  p.bm = rows_per_wg(kQBPlain);
-  RC_TRY(plan(L, RC_ENTRY_PREFILL, p));
-  const CopyPlan c = plan_copy_tail(p, count_cached_rows(L));
+  RC_TRY(plan_prefill(L, D, false, p));
   *attn_wgs = int64_t(B) * H * p.n_qtiles;
-  *copy_wgs = c.blocks;
-  *copy_rows = c.rows;
+  *copy_wgs = p.cp.blocks;
+  *copy_rows = p.cp.rows;
   return RC_OK;
 }
 
@@ -513,6 +528,34 @@ rc_status rc_step_launch_shape(const rc_layout* L, int32_t B, int32_t H, int32_t
                  : p.lr_tiles > 0            ? int64_t(B) * H * p.n_qtiles + p.lr_tiles
                                              : int64_t(B) * H * p.n_qtiles * p.splits;
   return RC_OK;
+}
+
+int64_t rc_attention_work_groups(const rc_layout* L, int32_t entry, int32_t B, int32_t H, int32_t D, int32_t splits,
+                                 int32_t fp8) {
+  using namespace rc;
+  RC_TRY(check_layout(L, entry));
+  RC_TRY(check_dims(B, H, D, 1.0f));
+  if (fp8 != 0 && fp8 != 1) {
+    set_error("rc_attention_work_groups: fp8 = %d must be 0 or 1", fp8);
+    return RC_ERR_ARG;
+  }
+  Params p;
+  memset(&p, 0, sizeof p);
+  fill_common(p, B, H, 1.0f);
+  if (entry == RC_ENTRY_STEP) {
+    int64_t wgs;
+    int32_t bm, used;
+    RC_TRY(rc_step_launch_shape(L, B, H, D, splits, fp8, &wgs, &bm, &used));  // checks splits
+    RC_TRY(plan_step(L, D, fp8 != 0, splits, p));
+  } else if (splits != 1 && !(entry == RC_ENTRY_FULL && splits == kSplitsLastRound)) {
+    set_error("rc_attention_work_groups: splits = %d", splits);
+    return RC_ERR_ARG;
+  } else if (entry == RC_ENTRY_FULL) {
+    RC_TRY(plan_full(L, splits == kSplitsLastRound, p));
+  } else {
+    RC_TRY(plan_prefill(L, D, fp8 != 0, p));
+  }
+  return attention_work_groups(p);
 }
 
 size_t rc_step_workspace_bytes(const rc_layout* L, int32_t B, int32_t H, int32_t D, int32_t splits) {
@@ -599,9 +642,9 @@ rc_status rc_full_attention_ws(const rc_layout* L, int32_t B, int32_t H, int32_t
   Params p;
   memset(&p, 0, sizeof p);
   fill_common(p, B, H, scale);
-  p.bm = rows_per_wg(kQBPlain);
-  RC_TRY(plan(L, RC_ENTRY_FULL, p));
-  RC_TRY(check_grid(p));
+  RC_TRY(plan_full(L, workspace != nullptr, p));
+  // the grid unsplit: the last-round split adds its pieces below
+  RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles, "attention"));
   p.q = static_cast<const uint16_t*>(q);
   p.q_st = tok_stride;
   p.q_sb = tok_stride * n;
@@ -610,28 +653,21 @@ rc_status rc_full_attention_ws(const rc_layout* L, int32_t B, int32_t H, int32_t
   p.o_sb = p.o_st * n;
   p.lse = lse;
   p.src[0] = bf16_source(k, v, tok_stride * n, D, tok_stride);
+  const int32_t T = p.lr_tiles;
   if (workspace) {
-    const int32_t T = last_round_tiles(p);
     const size_t need = size_t(2) * T * p.bm * size_t(D + 2) * sizeof(float);
     if (!aligned16(workspace) || ws_bytes < need) {
       set_error("the last-round split needs a 16-byte aligned workspace of %zu bytes (got %zu)", need, ws_bytes);
       return RC_ERR_WORKSPACE;
     }
-    if (T > 0) {
-      p.splits = 2;
-      p.lr_tiles = T;
-      p.ws_o = static_cast<float*>(workspace);
-      p.ws_ml = p.ws_o + size_t(2) * T * p.bm * D;
-      p.half_tiles = half_tiles(p);
-      RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + T, "full attention"));
-      RC_TRY(hip_status(launch_attention(p, D, stream), "full attention launch"));
-      RC_TRY(hip_status(launch_combine_last_round(p, D, stream), "last-round merge launch"));
-      return RC_OK;
-    }
-    p.tail_num = 0;
   }
-  p.half_tiles = half_tiles(p);
+  if (T > 0) {
+    p.ws_o = static_cast<float*>(workspace);
+    p.ws_ml = p.ws_o + size_t(2) * T * p.bm * D;
+    RC_TRY(check_blocks(int64_t(B) * H * p.n_qtiles + T, "full attention"));
+  }
   RC_TRY(hip_status(launch_attention(p, D, stream), "full attention launch"));
+  if (T > 0) RC_TRY(hip_status(launch_combine_last_round(p, D, stream), "last-round merge launch"));
   return RC_OK;
 }
 

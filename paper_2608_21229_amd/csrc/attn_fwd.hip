@@ -1793,10 +1793,7 @@ int scratch_address(void** ptr) {
 
 int launch_attention(const Params& p, int D, void* stream) {
   const int64_t tiles = int64_t(p.B) * p.H * p.n_qtiles;
-  // the last-round split adds one short piece per split tile; a tile (or
-  // piece) run as two halves adds one work-group
-  const int64_t blocks = p.lr_tiles > 0 ? tiles + p.lr_tiles + (p.half_tiles > 0 ? 2 * int64_t(p.lr_tiles) : 0)
-                                        : (tiles + p.half_tiles) * p.splits;
+  const int64_t blocks = attention_work_groups(p);
   if (blocks == 0) return 0;
   if (p.lr_tiles < 0 || (p.lr_tiles > 0 && (p.splits != 2 || p.tail_num <= 0 || p.lr_tiles > tiles)))
     return int(hipErrorInvalidValue);

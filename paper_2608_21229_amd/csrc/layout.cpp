@@ -414,6 +414,15 @@ int32_t half_tiles(const Params& p) {
   return 2 * A + p.cp.blocks <= kCUs ? int32_t(A) : 0;
 }
 
+int64_t attention_work_groups(const Params& p) {
+  if (p.splits == kSplitsBalanced) return p.bal_wgs;
+  const int64_t tiles = int64_t(p.B) * p.H * p.n_qtiles;
+  // the last-round split adds one short piece per split tile; a tile (or
+  // piece) run as two halves adds one work-group
+  if (p.lr_tiles > 0) return tiles + p.lr_tiles + (p.half_tiles > 0 ? 2 * int64_t(p.lr_tiles) : 0);
+  return (tiles + p.half_tiles) * p.splits;
+}
+
 int32_t tail_num(const Params& p) {
   // Q query tiles on Q CUs; 256 - Q CUs run the short pieces, R rounds each:
   // the long piece takes R / (R + 1) of the keys so both end together.

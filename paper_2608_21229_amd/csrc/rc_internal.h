@@ -190,6 +190,9 @@ int32_t last_round_tiles(Params& p);
 // How many of the last query tiles run as two work-groups of half the rows
 // (p.half_tiles), once splits, lr_tiles and cp.blocks are set.
 int32_t half_tiles(const Params& p);
+// Work-groups of the attention kernel over all its launches, without the
+// prefill's copy work-groups.
+int64_t attention_work_groups(const Params& p);
 // The prefill's bf16 cache store: the copy work-groups appended to the
 // attention grid and the flat cache rows [0, rows) they take; the store
 // kernel copies the rest.

@@ -44,20 +44,28 @@ def test_random_layouts_through_every_entry(preset):
         n0 = launches()
         assert _full(L, B=B, H=H, D=D, ts=ts, lse=FAKE) == rc.RC_OK
         assert launches() == n0 + (1 if sum(lens) else 0)
+        assert stub("rc_stub_work_groups") == L.work_groups(rc.ENTRY_FULL, B, H, D)
         # with the last-round split's workspace: the attention launch, plus the
         # merge when it splits
         need = L.full_workspace_bytes(B, H, D)
         n0 = launches()
         assert _full_ws(L, B=B, H=H, D=D, ts=ts, lse=FAKE, ws=FAKE, wsb=need) == rc.RC_OK
         assert launches() == n0 + (1 if sum(lens) else 0) + (1 if need else 0)
+        assert stub("rc_stub_work_groups") == L.work_groups(rc.ENTRY_FULL, B, H, D, rc.SPLITS_LAST_ROUND)
         if not om.is_cacheable(kinds, vis):
             assert _prefill(L, B=B, H=H, D=D, ts=ts) == rc.RC_ERR_MASK_NOT_CACHEABLE
             continue
         assert _prefill(L, B=B, H=H, D=D, ts=ts, lse=FAKE) == rc.RC_OK
+        if L.rows(rc.ROWS_STATIC):
+            assert stub("rc_stub_work_groups") == L.work_groups(rc.ENTRY_PREFILL, B, H, D)
+            assert _prefill_fp8(L, B, H, D) == rc.RC_OK
+            assert stub("rc_stub_work_groups") == L.work_groups(rc.ENTRY_PREFILL, B, H, D, fp8=True)
         for splits in (1, 2, 5, 0, rc.SPLITS_TAIL, rc.SPLITS_BALANCED, rc.SPLITS_LAST_ROUND):
             need = L.workspace_bytes(B, H, D, splits)
             st = _step(L, B=B, H=H, D=D, ts=ts, splits=splits, ws=FAKE if need else None, wsb=need, lse=FAKE)
             assert st == rc.RC_OK, (kinds, lens, splits, rc.lib().rc_last_error().decode())
+            if L.rows(rc.ROWS_LIVE):
+                assert stub("rc_stub_work_groups") == L.work_groups(rc.ENTRY_STEP, B, H, D, splits), splits
 
 
 @pytest.mark.parametrize("segs,mask,runs", [

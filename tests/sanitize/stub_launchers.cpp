@@ -18,6 +18,7 @@ namespace {
 
 long g_launches = 0;
 long g_runs = 0;  // runs of the last copy table
+long g_wgs = 0;   // work-groups of the last attention launch
 long g_heads = -1;  // (batch, head)s whose amax the last FP8 prefill's attention launch takes
 
 [[noreturn]] void fail(const char* what, long a, long b) {
@@ -109,6 +110,7 @@ int launch_attention(const Params& p, int D, void*) {
     REQUIRE(p.splits == 2 && p.tail_num > 0 && p.cp.blocks == 0, p.splits, p.tail_num);
     REQUIRE(p.lr_tiles <= int64_t(p.B) * p.H * p.n_qtiles, p.lr_tiles, p.n_qtiles);
   }
+  g_wgs = attention_work_groups(p);
   const CopyTail& c = p.cp;
   REQUIRE(c.blocks >= 0 && c.blocks <= kCUs, c.blocks, 0);
   if (c.blocks > 0) {
@@ -125,6 +127,7 @@ int launch_attention(const Params& p, int D, void*) {
 
 int launch_attention_balanced(const Params& p, int D, void*) {
   check_params(p, D, true);
+  g_wgs = attention_work_groups(p);
   ++g_launches;
   return 0;
 }
@@ -189,3 +192,4 @@ int scratch_address(void** ptr) {
 extern "C" long rc_stub_launches(void) { return g_launches; }
 extern "C" long rc_stub_copy_runs() { return g_runs; }
 extern "C" long rc_stub_amax_heads() { return g_heads; }
+extern "C" long rc_stub_work_groups() { return g_wgs; }

@@ -281,6 +281,41 @@ def test_step_launch_shape():
                                          ctypes.byref(sp)) == rc.RC_ERR_ARG
 
 
+def test_attention_work_groups():
+    """What is launched: the counts of the launch queries, with a tile or piece
+    run as two halves counted twice."""
+    head = [(0, 64), (1, 512), (2, 4096)]
+    L = rc.Layout(head + [(3, 4096)] * 5, "perref")
+    step = lambda H, splits=0, B=1, fp8=False: L.work_groups(rc.ENTRY_STEP, B, H, 128, splits, fp8)
+    assert step(24) == 216 and step(24, rc.SPLITS_TAIL) == 432 and step(24, rc.SPLITS_BALANCED) == 256
+    # one GPU's share: 27 tiles, unsplit in halves; nine splits fill the chip whole
+    assert step(3, 1) == step(3, 1, fp8=True) == 54 and step(3) == 243
+    # even splits of at most half a round in halves
+    assert step(3, 4) == 2 * 27 * 4 and step(3, 5) == 27 * 5
+    # last-round split: T = 32 as four halves each, T = 176 as two pieces
+    assert step(32) == 288 - 32 + 4 * 32 and step(24, B=2) == 432 + 176
+    pre = lambda lay, H, fp8=False: lay.work_groups(rc.ENTRY_PREFILL, 1, H, 128, fp8=fp8)
+    assert pre(L, 24) == 984
+    L1 = rc.Layout(head + [(3, 4096)], "perref")
+    assert pre(L1, 24) == 216 and pre(L1, 5) == pre(L1, 5, fp8=True) == 90
+    Lb = rc.Layout(head[1:] + [(3, 4096)] * 5, "dense")
+    full = lambda B, splits: Lb.work_groups(rc.ENTRY_FULL, B, 24, 128, splits)
+    assert full(1, 1) == 1176 and full(1, rc.SPLITS_LAST_ROUND) == 1176 + 152
+    assert full(2, 1) == 2352 and full(2, rc.SPLITS_LAST_ROUND) == 2352 - 48 + 4 * 48
+    assert Lb.work_groups(rc.ENTRY_FULL, 1, 2, 64) == 2 * 98
+    for args, status in (((rc.ENTRY_PREFILL, 1, 2, 128, 2), rc.RC_ERR_ARG),
+                         ((rc.ENTRY_FULL, 1, 2, 128, 0), rc.RC_ERR_ARG),
+                         ((rc.ENTRY_FULL, 1, 2, 128, rc.SPLITS_TAIL), rc.RC_ERR_ARG),
+                         ((rc.ENTRY_STEP, 1, 2, 128, 33), rc.RC_ERR_ARG),
+                         ((3, 1, 2, 128, 1), rc.RC_ERR_ARG), ((rc.ENTRY_STEP, 0, 2, 128, 1), rc.RC_ERR_ARG),
+                         ((rc.ENTRY_STEP, 1, 2, 96, 1), rc.RC_ERR_UNSUPPORTED),
+                         ((rc.ENTRY_STEP, 1, 2, 128, rc.SPLITS_BALANCED, True), rc.RC_ERR_UNSUPPORTED)):
+        with pytest.raises(rc.RcError) as e:
+            L.work_groups(*args)
+        assert e.value.status == status, args
+    assert rc.lib().rc_attention_work_groups(ctypes.byref(L.c), rc.ENTRY_STEP, 1, 2, 128, 1, 2) == rc.RC_ERR_ARG
+
+
 def test_full_last_round_split_workspace():
     """rc_full_workspace_bytes: 2 T 512 (D + 2) 4 bytes for the T query tiles
     of the grid's partial last round, when the idle CUs run at most three

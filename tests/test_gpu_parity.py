@@ -536,6 +536,8 @@ def test_half_tiles_match_whole_tiles(lens, D, fp8):
         torch.cuda.synchronize()
         return o, ol, lse
 
+    for H, halves in ((80, 1), (4, 2)):
+        assert L.work_groups(rc.ENTRY_STEP, 1, H, D, 1, fp8) == halves * L.launch_shape(1, H, D, 1, fp8)[0]
     whole = run(0, 80)
     half = run(3, 7)
     for a, b, d in ((whole[0], half[0], 2), (whole[1], half[1], 2), (whole[2], half[2], 1)):
@@ -578,6 +580,9 @@ def test_half_tiles_even_splits(lens, splits, few, D, fp8):
 
     whole, half = run(0, H, splits), run(3, 3 + few, splits)
     assert L.launch_shape(1, H, D, splits)[0] > 128 >= L.launch_shape(1, few, D, splits)[0]
+    for heads, halves in ((H, 1), (few, 2)):
+        assert (L.work_groups(rc.ENTRY_STEP, 1, heads, D, splits, fp8)
+                == halves * L.launch_shape(1, heads, D, splits, fp8)[0])
     assert torch.equal(whole[0][:, :, 3:3 + few], half[0])
     assert torch.equal(whole[1][:, 3:3 + few], half[1])
     one = run(3, 3 + few, 1)
