@@ -388,29 +388,30 @@ int32_t last_round_tiles(Params& p) {
 }
 
 int32_t half_tiles(const Params& p) {
-  // A tile in two work-groups of 256 rows takes 0.6 (either head_dim)
-  // of a whole one's time each on a full chip, 0.83 (D = 128) and 0.7 (D = 64)
-  // where the other half of the CUs was idle before (the clock falls), so it pays only where every
-  // extra work-group finds an idle CU.  The last-round split's two pieces of
-  // T <= 64 tiles: five references of 4096, 32 heads (T = 32) 1 229 -> 1 141
-  // us; T = 64 at D = 64 542 -> 483 us.  A whole unsplit grid of at most 128:
-  // 128 tiles of 256 key tiles 650 -> 537 us (D = 64 482 -> 332 us).  Even
-  // splits that few key tiles keep to half a round or less, where some tile
-  // has more than 256 rows: 12 to 24 heads, two to five splits of about eight
-  // key tiles 40 -> 33 us, 51 -> 42 us, 2 heads 39 -> 29 us.  (Counting only the halves that
-  // hold rows fits more grids, but the empty work-groups between them delay
-  // the others: 240 work-groups of one half each 45 -> 69 us.)  The last
-  // partial round of an unsplit grid, whose idle CUs the prefill's copy
-  // work-groups use, measured no better or slower (1 024-token references
-  // among 4 096: 642 -> 639-700 us).
+  // A tile in two work-groups of 256 rows takes 0.6 (either head_dim) of a
+  // whole one's time each on a full chip, 0.83 (D = 128) and 0.7 (D = 64)
+  // where the other half of the CUs was idle before (the clock falls), so it
+  // pays only where every extra work-group finds an idle CU, and only if some
+  // tile has more than 256 rows: a second half without rows is an empty
+  // work-group (the same time where all halves fit: 24 heads, segments of 256
+  // rows, 36 us with and without).  The last-round split's two pieces of T <= 64
+  // tiles: five references of 4096, 32 heads (T = 32) 1 229 -> 1 141 us; T = 64
+  // at D = 64 542 -> 483 us.  A whole unsplit grid of at most 128: 128 tiles of
+  // 256 key tiles 650 -> 537 us (D = 64 482 -> 332 us).  Even splits that few
+  // key tiles keep to half a round or less: 12 to 24 heads, two to five splits
+  // of about eight key tiles 40 -> 33 us, 51 -> 42 us, 2 heads 39 -> 29 us.
+  // (Counting only the halves that hold rows fits more grids, but the empty
+  // work-groups between them delay the others: 240 work-groups of one half
+  // each 45 -> 69 us.)  The last partial round of an unsplit grid, whose idle
+  // CUs the prefill's copy work-groups use, measured no better or slower
+  // (1 024-token references among 4 096: 642 -> 639-700 us).
+  bool gain = false;
+  for (int i = 0; i < p.n_qseg; ++i) gain = gain || p.qseg[i].len > p.bm / 2;
+  if (!gain) return 0;
   if (p.lr_tiles > 0) return 4 * p.lr_tiles <= kCUs ? p.lr_tiles : 0;
   if (p.splits < 1 || p.tail_num > 0) return 0;
   const int64_t A = int64_t(p.B) * p.H * p.n_qtiles;
-  if (p.splits > 1) {
-    bool gain = false;
-    for (int i = 0; i < p.n_qseg; ++i) gain = gain || p.qseg[i].len > p.bm / 2;
-    return gain && 2 * A * p.splits <= kCUs ? int32_t(A) : 0;
-  }
+  if (p.splits > 1) return 2 * A * p.splits <= kCUs ? int32_t(A) : 0;
   return 2 * A + p.cp.blocks <= kCUs ? int32_t(A) : 0;
 }
 

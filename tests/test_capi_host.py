@@ -316,6 +316,23 @@ def test_attention_work_groups():
     assert rc.lib().rc_attention_work_groups(ctypes.byref(L.c), rc.ENTRY_STEP, 1, 2, 128, 1, 2) == rc.RC_ERR_ARG
 
 
+@pytest.mark.parametrize("rows,halves", [(256, 1), (100, 1), (257, 2), (512, 2)])
+def test_no_halves_without_rows(rows, halves):
+    """A tile runs as two halves only where some tile has more than 256 rows:
+    otherwise every second half would be an empty work-group."""
+    L = rc.Layout([(0, 8), (1, rows), (2, 100), (3, rows), (3, 3000)], "perref")
+    Ls = rc.Layout([(0, 8), (1, 64), (3, rows), (3, 90)], "paper")
+    Lf = rc.Layout([(1, rows), (2, 100)], "dense")
+    for D in (64, 128):
+        for fp8 in (False, True):
+            assert L.work_groups(rc.ENTRY_STEP, 1, 5, D, 1, fp8) == halves * 10
+            assert L.work_groups(rc.ENTRY_STEP, 1, 5, D, 3, fp8) == halves * 30
+            assert Ls.work_groups(rc.ENTRY_PREFILL, 1, 5, D, fp8=fp8) == halves * 15
+        assert Lf.work_groups(rc.ENTRY_FULL, 1, 5, D) == halves * 10
+    # 131 heads: 262 tiles, the last 6 in two pieces each
+    assert L.work_groups(rc.ENTRY_STEP, 1, 131, 64, rc.SPLITS_LAST_ROUND) == 256 + 6 * 2 * halves
+
+
 def test_full_last_round_split_workspace():
     """rc_full_workspace_bytes: 2 T 512 (D + 2) 4 bytes for the T query tiles
     of the grid's partial last round, when the idle CUs run at most three

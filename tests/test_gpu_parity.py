@@ -512,9 +512,9 @@ def test_step_query_segment_without_keys(splits):
 @pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (64, True), (128, True)])
 @pytest.mark.parametrize("lens", [(300, 600), (256, 513), (1, 257)])
 def test_half_tiles_match_whole_tiles(lens, D, fp8):
-    """A grid of at most 128 query tiles runs every tile as two work-groups of
-    256 rows, and rows past a tile's first 256 may be few or none; a larger
-    grid runs whole tiles.  A head's rows are the same bits in both (the same
+    """A grid of at most 128 query tiles, some of more than 256 rows, runs every
+    tile as two work-groups of 256 rows, and rows past a tile's first 256 may
+    be few or none; a larger grid runs whole tiles.  A head's rows are the same bits in both (the same
     MFMA chains), against the oracle on sampled rows."""
     from synthgen import Workload
     lt, x = lens
