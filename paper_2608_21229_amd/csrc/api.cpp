@@ -279,8 +279,6 @@ rc_status prefill_impl(const rc_layout* L, int32_t B, int32_t H, int32_t D, floa
     if (c.bh0 > 0) {
       t.k_src = c.k_src;
       t.v_src = c.v_src;
-      t.k_dst = reinterpret_cast<uint16_t*>(c.k_dst);  // not written: the quantising store follows
-      t.v_dst = reinterpret_cast<uint16_t*>(c.v_dst);
       t.src_sb = c.src_sb;
       t.src_st = c.src_st;
       t.n_cached = c.n_cached;

@@ -1808,6 +1808,9 @@ int launch_attention(const Params& p, int D, void* stream) {
   // copy work-groups ride on unsplit bf16 grids only (the other kernels have
   // no copy path)
   if (p.cp.blocks < 0 || (p.cp.blocks > 0 && (p.splits != 1 || p.fp8))) return int(hipErrorInvalidValue);
+  // they copy into bf16 buffers, or take an amax and have none
+  if (p.cp.blocks > 0 && (p.cp.amax ? p.cp.k_dst || p.cp.v_dst : !p.cp.k_dst || !p.cp.v_dst))
+    return int(hipErrorInvalidValue);
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (p.cp.blocks > 0 && p.cp.amax) {
     const int n = p.cp.B * p.cp.H * 2;

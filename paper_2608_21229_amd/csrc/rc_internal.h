@@ -73,7 +73,7 @@ struct CopyTail {
   int32_t blocks;          // copy work-groups at the end of the grid (0: none)
   int32_t rows;            // flat cache rows (b, h, row) [0, rows) that they copy
   float* amax;             // FP8 cache: instead of copying, take the rows' largest magnitudes per (batch, head)
-                           // into [B, H, 2] (K, V), which a launch before has cleared
+                           // into [B, H, 2] (K, V), which a launch before has cleared; k_dst and v_dst are null
   CopySeg seg[RC_MAX_SEGMENTS];
 };
 

@@ -115,7 +115,9 @@ int launch_attention(const Params& p, int D, void*) {
   REQUIRE(c.blocks >= 0 && c.blocks <= kCUs, c.blocks, 0);
   if (c.blocks > 0) {
     REQUIRE(p.splits == 1 && !p.fp8, p.splits, p.fp8);
-    REQUIRE(c.k_src && c.v_src && c.k_dst && c.v_dst, 0, 0);
+    REQUIRE(c.k_src && c.v_src, 0, 0);
+    // bf16 buffers to copy into, or an amax to take and nothing to write
+    REQUIRE(c.amax ? !c.k_dst && !c.v_dst : c.k_dst && c.v_dst, c.amax != nullptr, c.k_dst != nullptr);
     REQUIRE(c.B == p.B && c.H == p.H, c.B, c.H);
     REQUIRE(int64_t(c.B) * c.H * c.n_cached < (int64_t(1) << 31), c.n_cached, 0);
     REQUIRE(c.rows >= c.blocks && c.rows <= int64_t(c.B) * c.H * c.n_cached, c.rows, c.blocks);
