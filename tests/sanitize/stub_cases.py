@@ -101,3 +101,10 @@ def test_amax_work_groups_take_all_heads_or_many(refs, mask, B, H, D, heads):
     some where that shortens the amax launch, or of none."""
     assert _prefill_fp8(rc.Layout(HEAD + [(3, n) for n in refs], mask), B, H, D) == rc.RC_OK
     assert stub("rc_stub_amax_heads") == heads
+
+
+@pytest.mark.parametrize("M,N,K,ld", [(1, 128, 64, 128), (300, 384, 192, 4096), (257, 256, 1 << 22, 1 << 22)])
+def test_linear_operands_reach_the_launch(M, N, K, ld):
+    n0 = launches()
+    assert rc.lib().rc_linear(M, N, K, FAKE, max(ld, K), FAKE, FAKE, max(ld, N), FAKE, max(ld, N), None) == rc.RC_OK
+    assert launches() == n0 + 1

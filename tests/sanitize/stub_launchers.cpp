@@ -4,12 +4,15 @@
 //
 // Every launcher checks the schedule it is handed against the invariants the
 // kernels rely on (segments and key ranges inside their tables, tile and unit
-// counts that add up, rows inside the buffers, the pointers a launch reads)
+// counts that add up, halved tiles on idle CUs, the merge's row blocks, the FP8
+// store's amax accumulators cleared and taken once, rows inside the buffers,
+// the pointers a launch reads)
 // and aborts with a message on the first violation; a clean call returns
 // hipSuccess (0) and counts the launch.
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "rc_internal.h"
@@ -19,6 +22,8 @@ namespace {
 long g_launches = 0;
 long g_runs = 0;  // runs of the last copy table
 long g_wgs = 0;   // work-groups of the last attention launch
+const float* g_amax = nullptr;  // accumulators that the last attention launch clears or takes maxima into
+long g_taken = 0;  // (batch, head)s whose amax it takes
 long g_heads = -1;  // (batch, head)s whose amax the last FP8 prefill's attention launch takes
 
 [[noreturn]] void fail(const char* what, long a, long b) {
@@ -85,6 +90,28 @@ void check_params(const rc::Params& p, int D, bool balanced) {
   }
 }
 
+// Tiles run as two halves: the last ones of one unsplit launch, all of an even
+// split or all of a last-round split, some of them with more than 256 rows,
+// every half on a CU of its own.
+void check_halves(const rc::Params& p) {
+  using namespace rc;
+  const int64_t tiles = int64_t(p.B) * p.H * p.n_qtiles;
+  REQUIRE(p.half_tiles >= 0 && p.half_tiles <= tiles, p.half_tiles, tiles);
+  if (p.half_tiles == 0) return;
+  bool gain = false;
+  for (int i = 0; i < p.n_qseg; ++i) gain = gain || p.qseg[i].len > p.bm / 2;
+  REQUIRE(gain && p.bm == rows_per_wg(2), p.bm, gain);
+  if (p.lr_tiles > 0) {
+    REQUIRE(p.half_tiles == p.lr_tiles && 4 * p.lr_tiles <= kCUs, p.half_tiles, p.lr_tiles);
+    return;
+  }
+  REQUIRE(p.tail_num == 0, p.tail_num, p.half_tiles);
+  REQUIRE(p.splits == 1 ? !per_batch_launches(p) : p.half_tiles == tiles, p.splits, p.half_tiles);
+  REQUIRE(attention_work_groups(p) + p.cp.blocks <= kCUs, attention_work_groups(p), p.cp.blocks);
+}
+
+bool aligned(const void* p, uintptr_t n) { return (reinterpret_cast<uintptr_t>(p) & (n - 1)) == 0; }
+
 void check_copy(const rc::CopySeg* seg, int n_copy, int32_t n_cached) {
   REQUIRE(n_copy >= 1 && n_copy <= RC_MAX_SEGMENTS, n_copy, 0);
   int64_t dst = 0;
@@ -110,8 +137,17 @@ int launch_attention(const Params& p, int D, void*) {
     REQUIRE(p.splits == 2 && p.tail_num > 0 && p.cp.blocks == 0, p.splits, p.tail_num);
     REQUIRE(p.lr_tiles <= int64_t(p.B) * p.H * p.n_qtiles, p.lr_tiles, p.n_qtiles);
   }
+  check_halves(p);
+  REQUIRE(aligned(p.ws_o, 16) && aligned(p.ws_ml, 8), 0, 0);
   g_wgs = attention_work_groups(p);
   const CopyTail& c = p.cp;
+  g_amax = c.blocks > 0 ? c.amax : nullptr;
+  g_taken = g_amax ? c.rows / c.n_cached : 0;
+  if (p.amax_clear) {
+    REQUIRE(p.splits == 1 && !p.fp8 && !g_amax && c.blocks == 0, p.splits, c.blocks);
+    REQUIRE(c.B == p.B && c.H == p.H, c.B, c.H);
+    g_amax = p.amax_clear;
+  }
   REQUIRE(c.blocks >= 0 && c.blocks <= kCUs, c.blocks, 0);
   if (c.blocks > 0) {
     REQUIRE(p.splits == 1 && !p.fp8, p.splits, p.fp8);
@@ -120,6 +156,7 @@ int launch_attention(const Params& p, int D, void*) {
     REQUIRE(c.amax ? !c.k_dst && !c.v_dst : c.k_dst && c.v_dst, c.amax != nullptr, c.k_dst != nullptr);
     REQUIRE(c.B == p.B && c.H == p.H, c.B, c.H);
     REQUIRE(int64_t(c.B) * c.H * c.n_cached < (int64_t(1) << 31), c.n_cached, 0);
+    REQUIRE(!c.amax || c.rows % c.n_cached == 0, c.rows, c.n_cached);
     REQUIRE(c.rows >= c.blocks && c.rows <= int64_t(c.B) * c.H * c.n_cached, c.rows, c.blocks);
     check_copy(c.seg, c.n_copy, c.n_cached);
   }
@@ -143,6 +180,7 @@ int launch_combine_balanced(const Params& p, int D, void*) {
 int launch_combine_last_round(const Params& p, int D, void*) {
   check_params(p, D, false);
   REQUIRE(p.lr_tiles > 0 && p.splits == 2 && p.ws_o && p.ws_ml, p.lr_tiles, p.splits);
+  REQUIRE(p.bm == rows_per_wg(2) && aligned(p.ws_o, 16) && aligned(p.ws_ml, 8), p.bm, 0);
   ++g_launches;
   return 0;
 }
@@ -151,6 +189,17 @@ int launch_combine(const CombineParams& c, void*) {
   REQUIRE(c.ws_o && c.ws_ml && c.o, 0, 0);
   REQUIRE(c.splits >= 2 && c.splits <= kMaxSplits, c.splits, 0);
   REQUIRE(c.n_rows >= 1 && (c.D == 64 || c.D == 128), c.n_rows, c.D);
+  REQUIRE(aligned(c.ws_o, 16) && aligned(c.ws_ml, 8) && aligned(c.o, 16), 0, 0);
+  // every row in one block of up to 32 rows of its segment
+  REQUIRE(c.n_seg >= 1 && c.n_seg <= RC_MAX_SEGMENTS, c.n_seg, 0);
+  int64_t row = 0, block = 0;
+  for (int i = 0; i < c.n_seg; ++i) {
+    REQUIRE(c.seg[i].len >= 1 && c.seg[i].row0 == row, i, c.seg[i].row0);
+    REQUIRE(c.seg[i].block0 == block, i, c.seg[i].block0);
+    row += c.seg[i].len;
+    block += (c.seg[i].len + 31) / 32;
+  }
+  REQUIRE(row == c.n_rows && block == c.n_blocks, c.n_rows, c.n_blocks);
   ++g_launches;
   return 0;
 }
@@ -169,6 +218,8 @@ int launch_cache_store_fp8(const CacheStore8Params& c, void*) {
   REQUIRE(c.n_cached <= kFp8MaxKeys, c.n_cached, 0);
   check_copy(c.seg, c.n_copy, c.n_cached);
   REQUIRE(c.bh0 >= 0 && c.bh0 <= c.B * c.H, c.bh0, c.B * c.H);
+  // the attention launch before has cleared the accumulators and taken the first heads
+  REQUIRE(g_amax == c.kv_scale && g_taken == c.bh0, g_taken, c.bh0);
   g_heads = c.bh0;
   ++g_launches;
   return 0;
@@ -178,6 +229,10 @@ int launch_linear(const LinearParams& q, void*) {
   REQUIRE(q.a && q.w && q.out, 0, 0);
   REQUIRE(q.M >= 1 && q.N >= 1 && q.K >= 1, q.M, q.N);
   REQUIRE(q.lda >= q.K && q.ldo >= q.N && (!q.r || q.ldr >= q.N), q.lda, q.ldo);
+  // 16-byte loads and stores of whole tiles, 32-bit offsets inside 256 rows
+  REQUIRE(q.N % 128 == 0 && q.K % 64 == 0, q.N, q.K);
+  REQUIRE(aligned(q.a, 16) && aligned(q.w, 16) && aligned(q.r, 16) && aligned(q.out, 16), 0, 0);
+  REQUIRE((q.lda | q.ldo | q.ldr) % 8 == 0 && 256 * 2 * std::max<int64_t>(q.lda, q.K) <= (int64_t(1) << 31), q.lda, q.K);
   ++g_launches;
   return 0;
 }
