@@ -146,24 +146,30 @@ def test_linear_headline_shapes_sampled_rows(N, resid):
                      f64(a[rows]), f64(w), None if r is None else f64(r[rows]))
 
 
-# One shape per output tile (256 x 256, 256 x 128, 128 x 128, 64 x 128, 64 x 64,
+# Two shapes per output tile (256 x 256, 256 x 128, 128 x 128, 64 x 128, 64 x 64,
 # each the cheapest in rounds over the CUs), rows and k slices off the tile and
-# ring edges: every row on a tile or block edge and the ragged last ones
-# against the oracle, and alone (its own call, in a 64 x 64 tile) bit for bit.
+# ring edges: one with few k slices, and one with more than twice as many as the
+# tile's ring holds (2, 3, 4, 6 and 8), an odd number.  Every row on a tile or
+# block edge and the ragged last ones against the oracle, and three rows alone
+# (their own calls, in a 64 x 64 tile) bit for bit.
 @pytest.mark.parametrize("M,N,K,resid", [
     (1537, 9216, 192, True),
     (600, 9344, 64, False),
     (300, 9216, 320, True),
     (150, 9216, 448, False),
     (65, 384, 192, True),
+    (1537, 9216, 320, False),
+    (600, 9344, 448, True),
+    (300, 9216, 576, False),
+    (150, 9216, 832, True),
+    (65, 384, 1088, False),
 ])
 def test_linear_every_tile(M, N, K, resid):
     a, w = _bf((M, K), 41 + M), _bf((N, K), 42 + N, K ** -0.5)
     r = _bf((M, N), 43 + K) if resid else None
     a_d, w_d, r_d = a.to(DEV), w.to(DEV), None if r is None else r.to(DEV)
     got = rc.linear(a_d, w_d, residual=r_d)
-    rows = sorted({i + d for i in range(0, M, 32) for d in (-1, 0) if 0 <= i + d} | {M - 1})[:40] + [M - 2, M - 1]
-    rows = sorted(set(rows))
+    rows = sorted({i + d for i in range(0, M, 32) for d in (-1, 0) if 0 <= i + d} | {M - 2, M - 1})
     torch.cuda.synchronize()
     want = oc.project(f64(a[rows]), f64(w), None if r is None else f64(r[rows]))
     check_projection(got[rows], want, f"linear tile M={M} N={N} K={K}", f64(a[rows]), f64(w),
@@ -175,10 +181,13 @@ def test_linear_every_tile(M, N, K, resid):
 
 
 # More than one round of 256 x 256 tiles: the last partial one in 64 x 128,
-# 128 x 128 or 256 x 128 parts, or whole; the last 64-row parts lie past M.  Every row against the same rows in calls of
-# their own (at most 64 tiles, one size), sampled rows against the oracle.
+# 128 x 128 or 256 x 128 parts, or whole; the last 64-row parts lie past M.  The
+# long K are more than twice the parts' rings (6, 4 and 3 slices).  Every row
+# against the same rows in calls of their own (at most 64 tiles, one size),
+# sampled rows against the oracle.
 @pytest.mark.parametrize("m_tiles,K,resid", [(33, 64, True), (36, 192, False), (40, 64, True), (44, 64, False),
-                                             (48, 128, False), (49, 64, True), (53, 64, False), (71, 64, False)])
+                                             (48, 128, False), (49, 64, True), (53, 64, False), (71, 64, False),
+                                             (33, 832, False), (36, 832, True), (40, 576, False), (44, 448, True)])
 def test_linear_cut_last_round(m_tiles, K, resid):
     M, N = 256 * m_tiles - 100, 2048
     a, w = _bf((M, K), 51 + M), _bf((N, K), 52, K ** -0.5)

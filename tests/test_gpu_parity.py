@@ -550,7 +550,7 @@ def test_half_tiles_match_whole_tiles(lens, D, fp8):
         check(whole[1], O, f"half tiles {lens} D={D}", rows)
 
 
-@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (64, True), (128, True)])
 @pytest.mark.parametrize("lens,splits,few", [((300, 600), 3, 4), ((256, 513), 10, 4), ((1, 257), 32, 2),
                                              ((520, 40), 2, 21)])
 def test_half_tiles_even_splits(lens, splits, few, D, fp8):
@@ -590,7 +590,7 @@ def test_half_tiles_even_splits(lens, splits, few, D, fp8):
     check_lse(half[1], f64(one[1]), f"half tiles {lens} splits={splits}")
 
 
-@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (128, True)])
+@pytest.mark.parametrize("D,fp8", [(64, False), (128, False), (64, True), (128, True)])
 @pytest.mark.parametrize("lens,splits", [((33, 31), 2), ((1, 64), 5), ((32, 95), 9), ((16, 520), 32),
                                          ((300, 700), rc.SPLITS_TAIL)])
 def test_split_merge_row_blocks(lens, splits, D, fp8):
