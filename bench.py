@@ -31,7 +31,9 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2608_21229_amd", "csrc", "attn_fwd.hip")
+# the attention kernel and what it includes of this repository
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_21229_amd", "csrc", f)
+                  for f in ("attn_fwd.hip", "rc_device.h", "rc_internal.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_fwd_ref5_step_traffic.txt")
 PAPER_CONTEXT = {
     "end_to_end_speedup_5_refs": 3.92,
@@ -45,7 +47,10 @@ def log(*a):
 
 
 def source_hash() -> str:
-    return hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for f in KERNEL_SOURCES:
+        h.update(open(f, "rb").read())
+    return h.hexdigest()[:16]
 
 
 def measured_counters(config: str):
