@@ -749,8 +749,8 @@ __device__ __forceinline__ void run_ring(const Params& p, const QSeg& qs, int b,
 // wave of a SIMD issues MFMAs the other one does its exp2/max/sum work, and
 // the two streams share the SIMD instead of taking turns.
 //
-// Group 1 alone loads the tiles (during its softmax phases), into a ring of
-// three stages: tile t + 2 is issued at the first softmax phase of tile t
+// Group 1 alone loads the tiles (during its softmax phases), at D = 128 into a
+// ring of three stages: tile t + 2 is issued at the first softmax phase of tile t
 // (the stage of tile t - 1 is free by then for both groups), and group 1
 // waits for tile t + 1 at the end of the MFMA phase that precedes group 0's
 // first read of it.  Sub-tiles past the range end are computed with every
@@ -881,11 +881,13 @@ __device__ __forceinline__ void mfma_phase(const uint16_t* vs, const uint16_t* k
 }
 
 // Barrier that starts an MFMA phase of the ping-pong ring.  The wave's LDS
-// reads still in flight are the phase's first V^T fragments, of the tile
-// being computed, which no load issued after this barrier overwrites (the
-// loads after a barrier refill the stage of the tile before), so unlike
-// ring_barrier it does not wait for them.  The empty asm statement keeps the
-// reads before the barrier.
+// reads still in flight are the phase's first V^T fragments, of tile t being
+// computed, so unlike ring_barrier it does not wait for them: the phase consumes
+// them before the wave's next barrier, and until that one the only tile that can
+// be loaded goes to the stage of tile t - 1 (D = 128: tile t + 2 of three stages;
+// D = 64, where only group 1 passes this barrier, before its last phase of tile
+// t: tile t + 3 of four).  The empty asm statement keeps the reads before the
+// barrier.
 __device__ __forceinline__ void mfma_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
@@ -995,7 +997,9 @@ __device__ __forceinline__ void pp_tile(const Params& p, int t, PPState& st, int
   pin_probs(pf, m_used, lsum);
   if constexpr (kF8) {
     // tile t + 2 (its codes landed; tile t + 3's may be in flight) widened into
-    // the stage of tile t - 1, which no wave reads any more
+    // a stage that no wave reads any more: that of tile t - 1 at D = 128, whose
+    // last phase ended at a barrier before for both groups; that of tile t - 2 at
+    // D = 64, where other waves of group 1 may still read tile t - 1
     if (grp == 1 && t + 2 < st.n) {
       if (t + 3 < st.n) wait_tiles_pp8<D>(1);
       else wait_tiles_pp8<D>(0);

@@ -25,7 +25,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kLinBK = 64;  // k per 128-byte LDS row
@@ -264,12 +263,13 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
 // A grid of 256 x 256 tiles whose last partial round is cut into smaller parts,
 // so that the round ends sooner: tiles from `whole` on (logical order) run in
 // parts of kPartM[part] x kPartN[part], on the CUs that become free.  Same bits
-// as whole tiles.  The chip is power-bound in full rounds (about 79 us each at
-// K = 3072: MFMAs in 71% of the cycles, at 1.74 GHz), so cutting only recovers
-// what a round's idle CUs do not give back in clock: 1.125 rounds of N = 9216,
-// K = 3072 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 -> 185, 4.2
-// rounds 361 -> 336; 1.1 rounds of N = K = 1024 49 -> 40 us.  The two smaller
-// parts run on four of the work-group's waves: as fast as on eight.
+// as whole tiles.  A round of whole tiles takes 77 us at K = 3072 in a grid of
+// four (MFMAs in 71% of the cycles, at 1.74 GHz; in one round 62%, at 1.91
+// GHz): the clock falls as more CUs work, so cutting only recovers what a
+// round's idle CUs do not give back in clock: 1.125 rounds of N = 9216, K = 3072
+// 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 -> 185, 4.2 rounds 361 ->
+// 336; 1.1 rounds of N = K = 1024 49 -> 40 us.  The two smaller parts run on
+// four of the work-group's waves: as fast as on eight.
 constexpr int kPartM[] = {64, 128, 256}, kPartN[] = {128, 128, 128};
 constexpr int parts_of(int part) { return 256 * 256 / (kPartM[part] * kPartN[part]); }
 struct LinCut {
@@ -311,12 +311,17 @@ void launch_tile(const LinearParams& q, hipStream_t s) {
 }
 
 // The tile of a call: the one whose rounds of 256 tiles (one work-group per
-// CU) cost least, at the measured cost of a round of each (us at K = 3072 with
-// the chip full; every tile's cost grows alike with K).  A larger tile reads
-// less per MFMA, a smaller one fills the chip: 1536 x 3072 x 3072 runs 72
-// tiles of 256 x 256 in 58 us, 144 of 256 x 128 in 34 us and 288 of 128 x 128
-// (a second round for 32 of them) in 45 us; 16 x 3072 x 3072, 52 us in 12
-// tiles of 256 x 256 and 12 us in 48 of 64 x 64.
+// CU) cost least, at the relative cost of a round of each, measured as one full
+// round at K = 3072 (us, launch included: 71, 41, 25, 18, 12; on another box 81,
+// 46, 27, 19, 12).  The ratios hold from K = 1024 on (35, 19, 12, 8.4, 6.0 us;
+// 2048: 58, 32, 19, 13, 8.8).  Below that the part of a round that does not grow
+// with K (12.0, 8.1, 5.8, 4.4, 4.3 us at K = 64) makes small tiles dearer than
+// rated, which moved no choice: the chosen tile was the fastest of the five, to
+// the noise, in all of 147 calls of 1 to 1000 rows, N = 384 to 8192 and K = 64 to
+// 3072.  A larger tile reads less per MFMA, a smaller one fills the chip: 1536 x
+// 3072 x 3072 runs 72 tiles of 256 x 256 in 58 us, 144 of 256 x 128 in 34 us and
+// 288 of 128 x 128 (a second round for 32 of them) in 45 us; 16 x 3072 x 3072,
+// 52 us in 12 tiles of 256 x 256 and 12 us in 48 of 64 x 64.
 struct LinTile {
   int bm, bn;
   int64_t cost;
@@ -340,7 +345,10 @@ int pick_linear(const LinearParams& q) {
 }
 
 // The cut of a call that would run more than one round of 256 x 256 tiles: the
-// smallest parts that still fit one round.  A last round more than half full
+// smallest parts that still fit one round.  It comes before pick_linear and does
+// not ask its costs: its whole rounds are what that would choose, except for
+// few rows and N above 65 000, where 256-row tiles are mostly padding (as before
+// smaller tiles existed).  A last round more than half full
 // stays whole, for its parts would need two rounds (256 x 128 and smaller ones
 // for 136 to 160 of 256 tiles measured within 1% of whole tiles either way,
 // for 176 2-7% slower).
