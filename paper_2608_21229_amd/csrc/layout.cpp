@@ -434,6 +434,67 @@ int32_t tail_num(const Params& p) {
   return int32_t(1024 * r / (r + 1));
 }
 
+// The tile of a call: the one whose rounds of 256 tiles (one work-group per
+// CU) cost least, a round costing a fixed part (first loads, stores) and a part
+// per 64-wide k slice, in ns, measured on full rounds: one round at K = 64, 1024
+// and 3072 takes 12.0, 35 and 81 us for 256 x 256, 8.1, 19 and 46 for 256 x 128,
+// 5.8, 12 and 26 for 128 x 128, 4.4, 8.4 and 19 for 64 x 128, 4.3, 6.0 and 12 for
+// 64 x 64, launch included; four rounds at K = 3072 308, 172, 102, 71, 47 (64 x
+// 128 is rated by calls of few rows, where its second round costs 12 us at K =
+// 1536).  Over 664 calls of 1 to 30 000 rows, N = 128 to 9216 and K = 64 to 3072
+// the tile chosen so was the fastest of the five but for six, at most 5% off.
+// (One cost for all K chose 128 x 128 over 256 x 128 for some rounds of few
+// slices: 4665 x 3456 x 64 17.0 us against 15.8.)  A larger tile reads less per
+// MFMA, a smaller one fills the chip: 1536 x 3072 x 3072 runs 72 tiles of 256 x
+// 256 in 58 us, 144 of 256 x 128 in 34 us and 288 of 128 x 128 (a second round
+// for 32 of them) in 45 us; 16 x 3072 x 3072, 52 us in 12 tiles of 256 x 256 and
+// 12 us in 48 of 64 x 64.
+static int32_t pick_linear(const LinearParams& q) {
+  struct {
+    int32_t bm, bn;
+    int64_t fixed, slice;
+  } constexpr kTiles[] = {
+      {256, 256, 5500, 1475}, {256, 128, 3700, 806}, {128, 128, 3200, 473}, {64, 128, 2500, 380}, {64, 64, 1800, 223}};
+  int32_t best = -1;
+  int64_t best_cost = 0;
+  for (int i = 0; i < 5; ++i) {
+    const auto& t = kTiles[i];
+    if (q.N % t.bn != 0) continue;
+    const int64_t tiles = (q.M + t.bm - 1) / t.bm * (q.N / t.bn);
+    const int64_t cost = (tiles + kCUs - 1) / kCUs * (t.fixed + t.slice * (q.K / 64));
+    if (best < 0 || cost < best_cost) {
+      best = i;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// The cut of a call that would run more than one round of 256 x 256 tiles: the
+// smallest parts that still fit one round.  It comes before the tile choice and
+// does not ask its costs: its whole rounds are what that would choose, except
+// for few rows and N above 65 000, where 256-row tiles are mostly padding (as
+// before smaller tiles existed).  A last round more than half full stays whole,
+// for its parts would need two rounds (256 x 128 and smaller ones for 136 to 160
+// of 256 tiles measured within 1% of whole tiles either way, for 176 2-7%
+// slower).
+LinearPlan plan_linear(const LinearParams& q) {
+  LinearPlan p{-1, -1, 0, 0};
+  if (q.N % 256 == 0) {
+    p.tiles = (q.M + 255) / 256 * (q.N / 256);
+    p.whole = p.tiles / kCUs * kCUs;
+    const int64_t rest = p.tiles - p.whole;
+    if (p.whole > 0 && rest > 0)
+      for (int32_t part = 0; part < 3; ++part)
+        if (rest * lin_parts(part) <= kCUs) {
+          p.part = part;
+          return p;
+        }
+  }
+  p.tile = pick_linear(q);
+  return p;
+}
+
 }  // namespace rc
 
 extern "C" {

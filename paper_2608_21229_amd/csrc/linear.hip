@@ -262,7 +262,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
 
 // A grid of 256 x 256 tiles whose last partial round is cut into smaller parts,
 // so that the round ends sooner: tiles from `whole` on (logical order) run in
-// parts of kPartM[part] x kPartN[part], on the CUs that become free.  Same bits
+// parts of kLinPartM[part] x 128, on the CUs that become free.  Same bits
 // as whole tiles.  A round of whole tiles takes 77 us at K = 3072 in a grid of
 // four (MFMAs in 71% of the cycles, at 1.74 GHz; in one round 62%, at 1.91
 // GHz): the clock falls as more CUs work, so cutting only recovers what a
@@ -270,14 +270,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_kernel(const LinearParams
 // 117 -> 96 us, 2.1 rounds 207 -> 178, 2.25 rounds 212 -> 185, 4.2 rounds 361 ->
 // 336; 1.1 rounds of N = K = 1024 49 -> 40 us.  The two smaller parts run on
 // four of the work-group's waves: as fast as on eight.
-constexpr int kPartM[] = {64, 128, 256}, kPartN[] = {128, 128, 128};
-constexpr int parts_of(int part) { return 256 * 256 / (kPartM[part] * kPartN[part]); }
-struct LinCut {
-  int64_t whole, tiles;  // tiles run whole, and in all
-  int part;
-};
-
-__global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, const LinCut cut) {
+__global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, const LinearPlan cut) {
   __shared__ __attribute__((aligned(1024))) char ring[kRingBytes<2, 2, 4, 2, 1, 3>];
   static_assert(sizeof(ring) >= size_t(kRingBytes<4, 2, 2, 4, 1, 2>), "ring");
   static_assert(sizeof(ring) >= size_t(kRingBytes<2, 2, 2, 2, 1, 4>), "ring");
@@ -289,10 +282,10 @@ __global__ __launch_bounds__(512) void linear_cut_kernel(const LinearParams q, c
     linear_tile<4, 2, 2, 4, 1, 2, 3>(q, ring, m0, n0);
     return;
   }
-  const int parts = parts_of(cut.part);
+  const int parts = lin_parts(cut.part);
   const int64_t w = lin_xcd_block(blockIdx.x - cut.whole, (cut.tiles - cut.whole) * parts);
   lin_tile<256, 256>(q, cut.whole + w / parts, m0, n0);
-  m0 += int(w % parts) / 2 * kPartM[cut.part];
+  m0 += int(w % parts) / 2 * kLinPartM[cut.part];
   n0 += int(w % parts) % 2 * 128;
   if (m0 >= q.M) return;
   if (cut.part < 2 && threadIdx.x >= 256) return;  // barriers wait for the waves that remain
@@ -310,71 +303,18 @@ void launch_tile(const LinearParams& q, hipStream_t s) {
   hipLaunchKernelGGL((linear_kernel<MB, NB, WM, WN, KS, ST, SP>), dim3(blocks), dim3(WM * WN * 64), 0, s, q);
 }
 
-// The tile of a call: the one whose rounds of 256 tiles (one work-group per
-// CU) cost least, at the relative cost of a round of each, measured as one full
-// round at K = 3072 (us, launch included: 71, 41, 25, 18, 12; on another box 81,
-// 46, 27, 19, 12).  The ratios hold from K = 1024 on (35, 19, 12, 8.4, 6.0 us;
-// 2048: 58, 32, 19, 13, 8.8).  Below that the part of a round that does not grow
-// with K (12.0, 8.1, 5.8, 4.4, 4.3 us at K = 64) makes small tiles dearer than
-// rated, which moved no choice: the chosen tile was the fastest of the five, to
-// the noise, in all of 147 calls of 1 to 1000 rows, N = 384 to 8192 and K = 64 to
-// 3072.  A larger tile reads less per MFMA, a smaller one fills the chip: 1536 x
-// 3072 x 3072 runs 72 tiles of 256 x 256 in 58 us, 144 of 256 x 128 in 34 us and
-// 288 of 128 x 128 (a second round for 32 of them) in 45 us; 16 x 3072 x 3072,
-// 52 us in 12 tiles of 256 x 256 and 12 us in 48 of 64 x 64.
-struct LinTile {
-  int bm, bn;
-  int64_t cost;
-};
-constexpr LinTile kLinTiles[] = {{256, 256, 71}, {256, 128, 41}, {128, 128, 25}, {64, 128, 18}, {64, 64, 12}};
-
-int pick_linear(const LinearParams& q) {
-  int best = -1;
-  int64_t best_cost = 0;
-  for (int i = 0; i < 5; ++i) {
-    const LinTile t = kLinTiles[i];
-    if (q.N % t.bn != 0) continue;
-    const int64_t tiles = ((q.M + t.bm - 1) / t.bm) * (q.N / t.bn);
-    const int64_t cost = (tiles + kCUs - 1) / kCUs * t.cost;
-    if (best < 0 || cost < best_cost) {
-      best = i;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
-// The cut of a call that would run more than one round of 256 x 256 tiles: the
-// smallest parts that still fit one round.  It comes before pick_linear and does
-// not ask its costs: its whole rounds are what that would choose, except for
-// few rows and N above 65 000, where 256-row tiles are mostly padding (as before
-// smaller tiles existed).  A last round more than half full
-// stays whole, for its parts would need two rounds (256 x 128 and smaller ones
-// for 136 to 160 of 256 tiles measured within 1% of whole tiles either way,
-// for 176 2-7% slower).
-bool plan_cut(const LinearParams& q, LinCut& cut) {
-  if (q.N % 256 != 0) return false;
-  cut.tiles = (q.M + 255) / 256 * (q.N / 256);
-  cut.whole = cut.tiles / kCUs * kCUs;
-  const int64_t rest = cut.tiles - cut.whole;
-  if (cut.whole == 0 || rest == 0) return false;
-  for (cut.part = 0; cut.part < 3; ++cut.part)
-    if (rest * parts_of(cut.part) <= kCUs) return true;
-  return false;
-}
-
 }  // namespace
 
 int launch_linear(const LinearParams& q, void* stream) {
   if (q.M == 0) return 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  LinCut cut;
-  if (plan_cut(q, cut)) {
-    const int64_t blocks = cut.whole + (cut.tiles - cut.whole) * parts_of(cut.part);
-    hipLaunchKernelGGL(linear_cut_kernel, dim3(blocks), dim3(512), 0, s, q, cut);
+  const LinearPlan plan = plan_linear(q);
+  if (plan.part >= 0) {
+    const int64_t blocks = plan.whole + (plan.tiles - plan.whole) * lin_parts(plan.part);
+    hipLaunchKernelGGL(linear_cut_kernel, dim3(blocks), dim3(512), 0, s, q, plan);
     return int(hipGetLastError());
   }
-  switch (pick_linear(q)) {
+  switch (plan.tile) {
     case 0: launch_tile<4, 2, 2, 4, 1, 2, 3>(q, s); break;
     case 1: launch_tile<2, 2, 4, 2, 1, 3, 8>(q, s); break;
     case 2: launch_tile<2, 2, 2, 2, 1, 4, 8>(q, s); break;

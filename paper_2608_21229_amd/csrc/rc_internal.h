@@ -158,6 +158,16 @@ struct LinearParams {
   int64_t lda, ldr, ldo;
 };
 
+// How rc_linear runs: a grid of one tile size (tile: 256 x 256, 256 x 128, 128 x
+// 128, 64 x 128, 64 x 64), or (part >= 0) `whole` tiles of 256 x 256 and the
+// other ones of `tiles` in parts of kLinPartM[part] x 128.
+struct LinearPlan {
+  int32_t tile, part;
+  int64_t whole, tiles;
+};
+constexpr int kLinPartM[] = {64, 128, 256};
+constexpr int lin_parts(int part) { return 256 / kLinPartM[part] * 2; }  // parts of a 256 x 256 tile
+
 struct CombineParams {
   const float* ws_o;
   const float* ws_ml;
@@ -190,6 +200,7 @@ int32_t last_round_tiles(Params& p);
 // How many of the last query tiles run as two work-groups of half the rows
 // (p.half_tiles), once splits, lr_tiles and cp.blocks are set.
 int32_t half_tiles(const Params& p);
+LinearPlan plan_linear(const LinearParams& q);
 // Work-groups of the attention kernel over all its launches, without the
 // prefill's copy work-groups.
 int64_t attention_work_groups(const Params& p);

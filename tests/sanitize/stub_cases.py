@@ -108,3 +108,42 @@ def test_linear_operands_reach_the_launch(M, N, K, ld):
     n0 = launches()
     assert rc.lib().rc_linear(M, N, K, FAKE, max(ld, K), FAKE, FAKE, max(ld, N), FAKE, max(ld, N), None) == rc.RC_OK
     assert launches() == n0 + 1
+
+
+def _linear_tile(M, N, K):
+    assert rc.lib().rc_linear(M, N, K, FAKE, K, FAKE, None, 0, FAKE, N, None) == rc.RC_OK
+    return stub("rc_stub_linear_tile")
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    # rounds of few slices, where a round's fixed part counts: the small tiles
+    # measured 5 to 16% slower than the ones chosen
+    (4665, 3456, 64, 1), (2700, 4224, 64, 1), (16350, 640, 64, 1), (299, 12032, 1024, 1), (1016, 8320, 64, 1),
+    (264, 11776, 64, 1), (547, 7040, 1536, 1), (539, 13952, 2560, 2),
+    # one round of each tile
+    (4096, 4096, 3072, 0), (1536, 3072, 3072, 1), (300, 9216, 320, 2), (150, 9216, 832, 3), (16, 3072, 3072, 4),
+    (1, 128, 64, 4),
+    # more than one round of 256 x 256: the rest in 64, 128 or 256-row parts, or whole
+    (256 * 33, 2048, 64, 5), (256 * 40, 2048, 64, 6), (256 * 44, 2048, 64, 7), (256 * 49, 2048, 64, 0),
+    (256 * 64, 2048, 64, 0),
+])
+def test_projection_tile(M, N, K, tile):
+    assert _linear_tile(M, N, K) == tile
+
+
+def test_projection_tile_costs_least():
+    """The rule on its own: the fewest nanoseconds in rounds of 256 work-groups,
+    each with a fixed part and one per 64-wide k slice."""
+    tiles = [(256, 256, 5500, 1475), (256, 128, 3700, 806), (128, 128, 3200, 473), (64, 128, 2500, 380),
+             (64, 64, 1800, 223)]
+    rng = random.Random(8)
+    for _ in range(400):
+        M, N, K = rng.randint(1, 1 << rng.randint(1, 15)), 128 * rng.randint(1, 110), 64 * rng.randint(1, 64)
+        got = _linear_tile(M, N, K)
+        cost = {i: -(-(-(-M // bm) * (N // bn)) // 256) * (f + s * (K // 64))
+                for i, (bm, bn, f, s) in enumerate(tiles) if N % bn == 0}
+        if got < 5:
+            assert cost[got] == min(cost.values()), (M, N, K)
+        else:
+            rest = -(-M // 256) * (N // 256) % 256
+            assert N % 256 == 0 and rest * (8, 4, 2)[got - 5] <= 256 and (got == 5 or rest * (8, 4, 2)[got - 6] > 256)

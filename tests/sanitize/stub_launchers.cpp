@@ -24,6 +24,7 @@ long g_runs = 0;  // runs of the last copy table
 long g_wgs = 0;   // work-groups of the last attention launch
 const float* g_amax = nullptr;  // accumulators that the last attention launch clears or takes maxima into
 long g_taken = 0;  // (batch, head)s whose amax it takes
+long g_linear = -1;  // tile of the last projection, or 5 + the part of a cut one
 long g_heads = -1;  // (batch, head)s whose amax the last FP8 prefill's attention launch takes
 
 [[noreturn]] void fail(const char* what, long a, long b) {
@@ -233,6 +234,16 @@ int launch_linear(const LinearParams& q, void*) {
   REQUIRE(q.N % 128 == 0 && q.K % 64 == 0, q.N, q.K);
   REQUIRE(aligned(q.a, 16) && aligned(q.w, 16) && aligned(q.r, 16) && aligned(q.out, 16), 0, 0);
   REQUIRE((q.lda | q.ldo | q.ldr) % 8 == 0 && 256 * 2 * std::max<int64_t>(q.lda, q.K) <= (int64_t(1) << 31), q.lda, q.K);
+  const LinearPlan p = plan_linear(q);
+  REQUIRE((p.tile >= 0) != (p.part >= 0) && p.tile < 5 && p.part < 3, p.tile, p.part);
+  const int bn[] = {256, 128, 128, 128, 64};
+  REQUIRE(q.N % (p.part >= 0 ? 256 : bn[p.tile]) == 0, q.N, p.tile);
+  if (p.part >= 0) {
+    REQUIRE(p.tiles == (q.M + 255) / 256 * (q.N / 256), p.tiles, q.M);
+    REQUIRE(p.whole > 0 && p.whole % kCUs == 0 && p.whole < p.tiles, p.whole, p.tiles);
+    REQUIRE((p.tiles - p.whole) * lin_parts(p.part) <= kCUs, p.tiles - p.whole, p.part);
+  }
+  g_linear = p.part >= 0 ? 5 + p.part : p.tile;
   ++g_launches;
   return 0;
 }
@@ -250,3 +261,4 @@ extern "C" long rc_stub_launches(void) { return g_launches; }
 extern "C" long rc_stub_copy_runs() { return g_runs; }
 extern "C" long rc_stub_amax_heads() { return g_heads; }
 extern "C" long rc_stub_work_groups() { return g_wgs; }
+extern "C" long rc_stub_linear_tile() { return g_linear; }
