@@ -344,21 +344,25 @@ CopyPlan plan_copy_tail(const Params& p, int64_t n_cached) {
 
 CopyPlan plan_amax_tail(const Params& p, int64_t n_cached, int32_t D) {
   // Whole (batch, head)s only.  All of them save the amax launch.  Some of
-  // them shorten it only where it is bound by bandwidth: below about 100 MB of
-  // K and V it takes about 20 us however many heads are left to it, so they
-  // would only lengthen the attention launch; and the plan's windows have to
-  // be long, for amax work-groups start later than its model says.
-  // Prefill us with none and with some of the heads in the attention launch:
-  // two entries of 24 heads, D = 64, 10 x 128 tokens (17 MB, window 3 tile
-  // times) 43 and 63; 40 heads, D = 64, 3 x 1024 (32 MB, 3) 70 and 90; 24
-  // heads, D = 128, 3 x 1519 (57 MB, 24) 117 and 130; 40 heads, D = 128, 5 x
-  // 4096 (421 MB, 64) 1652 and 1600.
-  constexpr int64_t kMinBytes = 96 << 20, kMinWindow = 32;
+  // them shorten it only where it is bound by bandwidth (it takes about 20 us
+  // however many heads are left to it), and lengthen the attention launch
+  // unless the plan's windows are long, for amax work-groups start later than
+  // its model says, most of all in a launch of one round, where they wait for
+  // short work-groups to leave.  Over 260 layouts, some heads against none: from
+  // 48 MB of K and V and windows of 20 tile times (32 in a launch of one round)
+  // on 0.973 to 1.004 of the time, otherwise up to 1.45.  Prefill us with none
+  // and with some: two entries of 24 heads, D = 64, 10 x 128 tokens (17 MB,
+  // window 3) 43 and 63; 40 heads, D = 64, 3 x 1024 (32 MB, 3) 70 and 90; 24
+  // heads, D = 128, 3 x 1519 (57 MB, 24, one round) 116 and 129; 24 heads, D =
+  // 128, 5 x 4096 (252 MB, 64) 948 and 941; 40 heads 1647 and 1585.
+  constexpr int64_t kMinBytes = 48 << 20;
   const CopyPlan none{0, 0};
   CopyPlan c = plan_copy_tail(p, n_cached);
   if (c.blocks == 0) return none;
   const int64_t heads = int64_t(p.B) * p.H, taken = c.rows / n_cached;
-  if (taken < heads && (heads * n_cached * D * 4 < kMinBytes || c.rows < c.blocks * kMinWindow * kCopyRowsPerTile))
+  const int64_t launch = (per_batch_launches(p) ? p.H : heads) * p.n_qtiles;
+  const int64_t window = launch > kCUs ? 20 : 32;
+  if (taken < heads && (heads * n_cached * D * 4 < kMinBytes || c.rows < c.blocks * window * kCopyRowsPerTile))
     return none;
   c.rows = taken * n_cached;
   return taken > 0 ? c : none;

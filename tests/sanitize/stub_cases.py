@@ -91,6 +91,9 @@ HEAD = [(0, 64), (1, 64), (2, 256)]
     ([1519] * 3, "perref", 1, 24, 128, 0),        # 13 of 24: 57 MB
     ([4096] * 8, "perref", 1, 24, 128, 0),        # 1 of 24: 403 MB, but windows of three tile times
     ([128] * 20, "paper", 1, 24, 64, 0),          # 8 of 24: long windows, 16 MB
+    ([1519] * 3, "perref", 2, 24, 128, 0),        # 13 of 48: 114 MB, but windows of 24 in launches of one round
+    ([1519] * 3, "perref", 3, 40, 128, 50),       # windows of 24, two rounds a launch
+    ([2304], "perref", 3, 40, 64, 54),            # one round a launch, windows of 36, 73 MB
     ([4096] * 5, "perref", 1, 24, 128, 12),       # 252 MB, windows of 64
     ([4096] * 5, "perref", 1, 40, 128, 38),
     ([4096] * 3, "perref", 1, 24, 128, 24),       # all of them
